@@ -24,6 +24,11 @@ __device__ __forceinline__ int wave_min(int v) {
 // every k < 2^16.
 __device__ __forceinline__ int split_row(int k, float inv) { return (int)(((float)k + 0.5f) * inv); }
 
+// 1/w for split_row: the hardware reciprocal (1 ulp) instead of the correctly
+// rounded division's ten instructions. The product then errs by under
+// (k / w) * 2^-21, still less than 1/(2w) for every k < 2^16.
+__device__ __forceinline__ float window_inv(int w) { return __builtin_amdgcn_rcpf((float)w); }
+
 // Workgroups of a launch are dispatched round-robin over the XCDs, each with
 // its own L2. Tile of linear workgroup id b among n: XCD x = b % XCDS takes a
 // contiguous run of tiles (row-major), so neighbouring tiles, which share

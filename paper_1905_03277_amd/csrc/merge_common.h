@@ -80,9 +80,12 @@ __host__ __device__ __forceinline__ Bounds footprint(double pxa, double pxb, dou
 // every bilinear corner, unclamped (edge values repeated); luma window: the
 // clamped corners' 3x3 neighbourhoods, whose outer ring may lie one quad
 // outside the grid and then repeats the edge quad (so Omega reads it without
-// clamping); raw window: the quads inside the grid and every nine-sample
-// window, unclamped (zero outside the frame). raw, lum, om: the window's
-// offsets in the LDS buffers.
+// clamping); raw window: the luma window's quads, unclamped (zero outside the
+// frame), which hold every nine-sample window: with p = 2k + f (0 <= f < 2)
+// its samples reach columns 2k - 1 .. 2k + 2, and the luma window quads k - 2
+// .. k + 1 where f < 1 and k - 1 .. k + 2 elsewhere; at the frame's edges the
+// centres stop at -1 and W and the luma window at quads -1 and w. raw, lum,
+// om: the window's offsets in the LDS buffers.
 struct Win {
   int rc0, rr0, rw, rh;
   int lc0, lr0, lw, lh;
@@ -97,17 +100,13 @@ __host__ __device__ __forceinline__ Win make_win(const Bounds& bd, const Geometr
   w.or0 = bd.hi0;
   w.oh = bd.hi1 - bd.hi0 + 2;
   w.lc0 = clampi(bd.hj0, 0, g.w - 1) - 1;
-  const int lc1 = clampi(bd.hj1 + 1, 0, g.w - 1) + 1;
+  w.lw = clampi(bd.hj1 + 1, 0, g.w - 1) + 2 - w.lc0;
   w.lr0 = clampi(bd.hi0, 0, g.h - 1) - 1;
-  const int lr1 = clampi(bd.hi1 + 1, 0, g.h - 1) + 1;
-  w.rc0 = min(2 * max(w.lc0, 0), bd.jc0 - 1);
-  const int rc1 = max(2 * min(lc1, g.w - 1) + 1, bd.jc1 + 1);
-  w.rr0 = min(2 * max(w.lr0, 0), bd.ic0 - 1);
-  const int rr1 = max(2 * min(lr1, g.h - 1) + 1, bd.ic1 + 1);
-  w.lw = lc1 - w.lc0 + 1;
-  w.lh = lr1 - w.lr0 + 1;
-  w.rw = rc1 - w.rc0 + 1;
-  w.rh = rr1 - w.rr0 + 1;
+  w.lh = clampi(bd.hi1 + 1, 0, g.h - 1) + 2 - w.lr0;
+  w.rc0 = 2 * w.lc0;
+  w.rw = 2 * w.lw;
+  w.rr0 = 2 * w.lr0;
+  w.rh = 2 * w.lh;
   w.raw = w.lum = w.om = 0;
   return w;
 }
