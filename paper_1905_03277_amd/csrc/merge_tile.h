@@ -34,10 +34,14 @@
 // than its arithmetic. Loading the window by single samples (index, bounds
 // and conversion per sample, then a pass over LDS for the quad sums) and
 // recomputing a column's position, fractions and offsets for each of its
-// pixels took 1.285 ms for the 12 MP x 8 merge, with quads, columns, colours
+// pixels took 1.285 ms for the 12 MP x 8 merge; with quads, columns, colours
 // from two parities, staged footprints and one barrier fewer per frame (three
-// instead of four and a load round trip) 1.009 ms; 15 x 1512 x 2016 at scale 2
-// 1.642 -> 1.337 ms; 8 x 256 x 256 82.8 -> 64.3 us.
+// instead of four and a load round trip) 1.009 ms; with Omega free of
+// branches, rows addressed from a vector register and the windows first in
+// LDS 0.985 ms (15 x 1512 x 2016 at scale 2: 1.642, 1.337, 1.287 ms; 8 x 256 x
+// 256: 82.8, 64.3, 62.3 us). Slower, by 1-4 %: Omega's three values
+// interleaved per entry, the interior flag as an integer, the staging's
+// threads rotated over the waves.
 #pragma once
 
 #include <math.h>
@@ -59,16 +63,17 @@ template <int MH>
 struct MergeSmem {
   using CP = Caps<MH>;
   static constexpr int NV = 2 * CP::VT;  // displacements staged at once (at least two frames')
+  // the windows first: their addresses then fit the instructions' offsets
+  float2 sRaw[CP::RAW / 2];
+  double sOm[3][CP::OM];
+  float sLum[CP::LUMA];
+  float sRh[CP::RH];
   double sX[MW], sY[MH];
   int sTyRow[MH], sTxCol[MW];
   int sRlo[CP::TY], sRhi[CP::TY], sClo[CP::TX], sChi[CP::TX];
   RowInfo sRow[MH];
   float2 sV[NV];    // displacement per frame slot and alignment tile (slot * ntiles + tile)
   int sBox[FCH][8];  // footprint of the whole tile per frame slot: Bounds, upper ends negated
-  float2 sRaw[CP::RAW / 2];
-  float sLum[CP::LUMA];
-  double sOm[3][CP::OM];
-  float sRh[CP::RH];
   Win sWin[CP::VT];    // per alignment tile, when the whole tile's window does not fit
   int sGrp[CP::VT + 1];  // groups of alignment tiles whose windows fit side by side
   int sNGrp;
@@ -209,6 +214,10 @@ __device__ __forceinline__ void merge_tile(const uint16_t* __restrict__ frames,
   // colour of Bayer position (r, c): green where r + c has parity gpar, and
   // the other colour of a row is red where the row has parity rpar
   const int rpar = g.red_pos >> 1, gpar = (rpar ^ g.red_pos ^ 1) & 1;
+  // this wave's rows, addressed from a vector register (as scalars they were
+  // spilled and read back for every pixel)
+  const RowInfo* rowv = sRow + (tid >> 6) * PX;
+  const double* yv = sY + (tid >> 6) * PX;
 
   // ---- accumulators -----------------------------------------------------
   using Acc = typename std::conditional<SAVE, double, float>::type;
@@ -294,7 +303,7 @@ __device__ __forceinline__ void merge_tile(const uint16_t* __restrict__ frames,
     for (int i = 0; i < QB; ++i) {
       const int k = min(k0 + i * THREADS, nq - 1);
       const int r = split_row(k, inv), c = k - mul24(r, w.lw);
-      const int I = clampi(w.lr0 + r, 0, g.h - 1), J = clampi(w.lc0 + c, 0, g.w - 1);
+      const int I = min(max(w.lr0 + r, 0), g.h - 1), J = min(max(w.lc0 + c, 0), g.w - 1);
       const int o = (int)((unsigned)I * (unsigned)(4 * g.W)) + 4 * J;  // bytes, below 2^31
       top[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, o, 0, 0);
       bot[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, o, 2 * g.W, 0);
@@ -341,7 +350,7 @@ __device__ __forceinline__ void merge_tile(const uint16_t* __restrict__ frames,
   };
   // Omega at entry (r, c) of window w, stored at flat entry e
   auto omega_at = [&](int e, const Win& w, int r, int c) {
-    const int I = clampi(w.or0 + r, 0, g.h - 1), J = clampi(w.oc0 + c, 0, g.w - 1);
+    const int I = min(max(w.or0 + r, 0), g.h - 1), J = min(max(w.oc0 + c, 0), g.w - 1);  // one v_med3 each
     // the window's outer ring repeats the edge quads: no clamps here
     const int base = w.lum + mul24(I - 1 - w.lr0, w.lw) + (J - 1 - w.lc0);
     float l[3][3];
@@ -392,19 +401,20 @@ __device__ __forceinline__ void merge_tile(const uint16_t* __restrict__ frames,
     cl.raw = w.raw + cl.jc - 1 - w.rc0 - mul24(w.rr0 + 1, w.rw);
   };
 
+  // R_hat at the thread's pixel row p
+  auto rho_at = [&](int p) __attribute__((always_inline)) {
+    const RowInfo ri = rowv[p];
+    const float* h = sRh + ri.ya + rxa;
+    const float top = h[0] + rfx * (h[1] - h[0]);
+    const float bot = h[rhw] + rfx * (h[rhw + 1] - h[rhw]);
+    return top + ri.fy * (bot - top);
+  };
+
   // accumulate: one pixel of column cl
-  auto pixel = [&](const int p, const int r, bool is_ref, bool inner, const Column& cl)
+  auto pixel = [&](const int p, const float rho, bool inner, const Column& cl)
                    __attribute__((always_inline)) {
-    float rho = 1.f;
-    if (!is_ref) {
-      const RowInfo ri = sRow[r];
-      const float* q = sRh + ri.ya + rxa;
-      const float top = q[0] + rfx * (q[1] - q[0]);
-      const float bot = q[rhw] + rfx * (q[rhw + 1] - q[rhw]);
-      rho = top + ri.fy * (bot - top);
-      if (!(rho > 0.f)) return;
-    }
-    const double py = sY[r] + (double)cl.vy;
+    if (!(rho > 0.f)) return;
+    const double py = yv[p] + (double)cl.vy;
     const double fic = floor(py);
     const double fry = py - fic;  // exact
     const int ic = (int)fic;
@@ -433,7 +443,7 @@ __device__ __forceinline__ void merge_tile(const uint16_t* __restrict__ frames,
     // the forward that keeps its normaliser, whose weights the adjoint
     // recomputes in float64 and must reproduce.
     const double sc = NEG_HALF_LOG2E * recip64_1(O[0] * O[2] - O[1] * O[1]);
-    const EF qa = (EF)(O[2] * sc), qb2 = (EF)(-2.0 * O[1] * sc), qc = (EF)(O[0] * sc);
+    const EF qa = (EF)(O[2] * sc), qb2 = (EF)-2 * (EF)(O[1] * sc), qc = (EF)(O[0] * sc);
     EF dy[3];
     {
       const EF fy0 = (EF)fry;
@@ -674,6 +684,15 @@ __device__ __forceinline__ void merge_tile(const uint16_t* __restrict__ frames,
         if (gi + 1 == ngroups && slot + 1 < nf) prefetch(slot + 1);
         if (col_ok) {
           const bool inner = F.whole && F.inner;
+          // every row's R_hat at once, so that their LDS round trips overlap
+          // (15 x 3 MP at scale 2: 1.305 -> 1.295 ms); the forward that keeps
+          // its normaliser has no registers to spare for them (1.20 -> 1.26
+          // ms for the training burst) and takes them one by one
+          float rho[PX];
+          if (!SAVE) {
+#pragma unroll
+            for (int p = 0; p < PX; ++p) rho[p] = is_ref ? 1.f : rho_at(p);
+          }
           Column cl;
           int had = -1;
           bool active = true;
@@ -692,7 +711,7 @@ __device__ __forceinline__ void merge_tile(const uint16_t* __restrict__ frames,
               }
               had = tyl;
             }
-            if (active) pixel(p, r, is_ref, inner, cl);
+            if (active) pixel(p, SAVE ? (is_ref ? 1.f : rho_at(p)) : rho[p], inner, cl);
           }
         }
       }

@@ -91,20 +91,21 @@ __device__ __forceinline__ void omega_core(const Q (&l)[3][3], const OmegaConsts
   const double half = 0.5 * (txx - tyy);
   const double r2 = half * half + txy * txy;
   const double tr = txx + tyy;
-  double rad = 0.0, c2 = 1.0, s2 = 0.0, A = 1.0;
-  if (r2 > 0.0) {
-    const double y = rsqrt64_1(r2);  // 1 / rad
-    rad = r2 * y;
-    c2 = half * y;
-    s2 = txy * y;
-    // A = 1 + sqrt((lambda1 - lambda2) / (lambda1 + lambda2)) = 1 + 1 / sqrt(tr / (2 rad)),
-    // with tr >= 2 rad > 0
-    A = 1.0 + rsqrt64_1(0.5 * tr * y);
-  }
+  // (tr and r2 are 0 or at least 1, being sums of integer products and their
+  // halves: the bounds below change nothing but what 0 would divide)
+  const bool some = r2 > 0.0;
+  const double y = rsqrt64_1(fmax(r2, 1e-300));  // 1 / rad
+  const double rad = r2 * y;
+  const double c2 = some ? half * y : 1.0;
+  const double s2 = txy * y;
+  // A = 1 + sqrt((lambda1 - lambda2) / (lambda1 + lambda2)) = 1 + 1 / sqrt(tr / (2 rad)),
+  // with tr >= 2 rad > 0; 1 (to 1e-74) where rad = 0
+  const double A = 1.0 + rsqrt64_1(0.5 * fmax(tr, 1.0) * y);
   const double invA = recip64_1(A);
-  const double sqrt_l1 = sqrt64_1(0.5 * tr + rad);
+  const double l1 = 0.5 * tr + rad;
+  const double sqrt_l1 = l1 * rsqrt64_1(fmax(l1, 1e-300));
   const double D_raw = 1.0 - sqrt_l1 * c.inv_16_range_dtr + c.d_th;
-  const double D = D_raw < 0.0 ? 0.0 : (D_raw > 1.0 ? 1.0 : D_raw);
+  const double D = fmin(fmax(D_raw, 0.0), 1.0);
   const double k1s = (1.0 - D) * (c.kd_st * A) + D * c.kd_dn;
   const double k2s = (1.0 - D) * (c.kd_sh * invA) + D * c.kd_dn;
   const double k1 = k1s * k1s, k2 = k2s * k2s;
