@@ -13,6 +13,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "device_util.h"
 #include "hmfsr_internal.h"
@@ -91,13 +92,12 @@ struct MatchLevel {
 // level whose pixels sum m raw values. The operations are rounded one by one
 // in this order (no contraction), so that every caller takes the same
 // decision for the same integers.
-__device__ __forceinline__ bool gate_moves(const MatchLevel& ml, int npx, long long S, unsigned long long gain) {
+__device__ __forceinline__ bool gate_moves(const MatchLevel& ml, int npx, long long S, double g) {
   const double n = (double)npx;
   const double nm = __dmul_rn(n, (double)(1ll << (2 * ml.level + 2)));
   double e = __dsub_rn((double)S, __dmul_rn(nm, ml.black));
   e = fmin(fmax(e, 0.0), __dmul_rn(nm, ml.rng));
   const double u = __dadd_rn(__dmul_rn(__dmul_rn(ml.na, ml.rng), e), __dmul_rn(__dmul_rn(__dmul_rn(nm, ml.nb), ml.rng), ml.rng));
-  const double g = (double)gain;
   return __dmul_rn(__dmul_rn(n, g), g) > __dmul_rn(__dmul_rn(ml.k12, u), u);
 }
 
@@ -315,7 +315,7 @@ __global__ __launch_bounds__(256) void k_align_match(const int32_t* __restrict__
         S += __shfl_xor(S, m, LPG);
         ssd_c += __shfl_xor(ssd_c, m, LPG);
       }
-      keep = !gate_moves(ml, nby * nbx, S, ssd_c - best.ssd);
+      keep = !gate_moves(ml, nby * nbx, S, (double)(ssd_c - best.ssd));
     }
     if (valid && l == 0) {
       const int k = keep ? kc : best.tie & 0xffff;
@@ -323,6 +323,220 @@ __global__ __launch_bounds__(256) void k_align_match(const int32_t* __restrict__
       vecs[(long long)f * vstride + ml.voff + t] = make_int2(gx + dxi - R, gy + dyi - R);
     }
     wave_sync();  // the next blocks restage this wave's LDS
+  }
+}
+
+// ---- block matching by rows --------------------------------------------------------
+// Blocks of 8, 16 or 32 pixels on levels 0-3 with radius 2 or 4 (the defaults
+// for every usual tile size). A lane owns an 8-pixel piece of a block row:
+// its template piece stays in registers, and for each vertical offset it reads
+// the 8 + 2R pixels of the frame that the 2R + 1 horizontal offsets share
+// (three or four 16-byte loads) straight from the level, so no index is
+// computed and no LDS read per candidate and pixel. The lane's partial sums
+// go to LDS, and the block's lanes then add one candidate each over the
+// pieces. B = 8: eight blocks per wave, 16: two, 32: one (two pieces a lane).
+//
+// A piece's sum of eight squared differences stays below 2^53 while a level's
+// values are below 2^25 (levels 0-3 of 16-bit frames), so float64 holds it
+// exactly; over the block it does below 2^22 (levels 0-2), and WIDE (level 3)
+// adds the pieces as 64-bit integers.
+//
+// Bound by the VALU (25 candidates x 8 pixels x a float64 difference and a
+// fused multiply-add per lane and pass, 4.4 cycles each) and, with three waves
+// per SIMD (13 KB of LDS a wave), the loads' latency. With a candidate per
+// lane and the block and its search region in LDS (two reads, a conversion and
+// index arithmetic per candidate and pixel) 12 MP x 8 took 245 us on level 0,
+// now 105; 5 x 510 x 766 with 32-pixel tiles took 38 us on the coarsest level
+// and 26 on each other one, now 11 and 7.5.
+template <int B>
+struct RowBlocks {
+  static constexpr int PPR = B / 8;                             // pieces per block row
+  static constexpr int LPB = B * PPR < 64 ? B * PPR : 64;       // lanes per block
+  static constexpr int SEG = B * PPR / LPB;                     // pieces per lane
+  static constexpr int BPW = 64 / LPB;                          // blocks per wave
+  // Lane of piece q of block b: the wave's blocks side by side within a row,
+  // so that lanes next to each other read memory next to each other.
+  __host__ __device__ static constexpr int lane_of(int b, int q) {
+    return q / PPR * (BPW * PPR) + b * PPR + q % PPR;
+  }
+  // Place of a lane's partial sum of candidate k: permuted by k, so that lanes
+  // adding different candidates read different banks.
+  __device__ static int slot(int k, int lane) { return k * 64 + (lane ^ (B == 8 ? (k & 3) << 3 : k & 31)); }
+};
+
+// 4 x NV consecutive words at byte offset voff + soff (four-byte aligned).
+template <int NV>
+__device__ __forceinline__ void ld_words(__amdgpu_buffer_rsrc_t rs, int voff, int soff, int32_t (&v)[4 * NV]) {
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const auto q = __builtin_amdgcn_raw_buffer_load_b128(rs, voff + 16 * i, soff, 0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[4 * i + j] = (int32_t)q[j];
+  }
+}
+
+// WPP: waves that share one group of blocks (they split the vertical offsets;
+// wave 0 then adds the candidates up).
+template <int B, int R, bool WIDE, int WPP>
+__global__ __launch_bounds__(256) void k_align_match_rows(const int32_t* __restrict__ pyr, int2* __restrict__ vecs,
+                                                          MatchLevel ml, int ref, long long fstride,
+                                                          long long vstride, int per_frame, int passes) {
+  using RB = RowBlocks<B>;
+  constexpr int LPB = RB::LPB, SEG = RB::SEG, BPW = RB::BPW, PPR = RB::PPR;
+  constexpr int D = 2 * R + 1, K = D * D, NV = (8 + 2 * R) / 4;
+  extern __shared__ double part[];  // per pass: [K][64] partial sums
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  double* pw = part + wave / WPP * (K * 64);
+  const int dy0 = wave % WPP;
+  const int blk = lane / PPR % BPW, lb = lane / (BPW * PPR) * PPR + lane % PPR;  // lane = lane_of(blk, lb)
+  const int h = ml.h, w = ml.w, per = ml.gby * ml.gbx;
+  const int p = xcd_tile(blockIdx.x, gridDim.x) * ((blockDim.x >> 6) / WPP) + wave / WPP;
+  const __amdgpu_buffer_rsrc_t rs_base = words_rsrc(pyr + (long long)ref * fstride + ml.loff, (long long)h * w);
+  if (p >= passes) return;  // the waves of a pass share p
+  const int fi = p / per_frame, f = fi < ref ? fi : fi + 1;  // one frame per pass: uniform
+  const int t0 = (p - fi * per_frame) * BPW + blk;
+  const bool valid = t0 < per;
+  const int t = valid ? t0 : per - 1;
+  const int by = t / ml.gbx, bx = t - by * ml.gbx;
+  const __amdgpu_buffer_rsrc_t rs = words_rsrc(pyr + (long long)f * fstride + ml.loff, (long long)h * w);
+  int gx = 0, gy = 0;
+  if (ml.parent) {
+    const int cy = min(((2 * by + 1) * B) / (4 * ml.pB), ml.pgby - 1);
+    const int cx = min(((2 * bx + 1) * B) / (4 * ml.pB), ml.pgbx - 1);
+    const int2 pv = vecs[(long long)f * vstride + ml.pvoff + cy * ml.pgbx + cx];
+    gx = 2 * pv.x;
+    gy = 2 * pv.y;
+  }
+  const int y0 = by * B, x0 = bx * B;
+  const int nby = min(B, h - y0), nbx = min(B, w - x0);
+  // every block of the wave whole, its search region inside the level: vector
+  // loads without clamps
+  const bool inside = nby == B && nbx == B && y0 + gy >= R && y0 + gy + B + R <= h && x0 + gx >= R &&
+                      x0 + gx + B + R <= w;
+  const bool fast = __all(inside);
+  // the frame's row under each of the lane's pieces at vertical offset dy
+  // (edge-replicated), the base frame's piece, all loads before any use
+  int32_t cur[SEG][4 * NV];
+  auto load_region = [&](int dy) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < SEG; ++s) {
+      const int q = lb + s * LPB, row = y0 + gy - R + q / PPR, col = x0 + gx - R + 8 * (q % PPR);
+      if (fast) {
+        ld_words<NV>(rs, (row * w + col) * 4, dy * w * 4, cur[s]);
+      } else {
+        const int yy = clampi(row + dy, 0, h - 1) * w;
+#pragma unroll
+        for (int c = 0; c < 4 * NV; ++c) cur[s][c] = ld_word(rs, yy + clampi(col + c, 0, w - 1));
+      }
+    }
+  };
+  load_region(dy0);
+  double tp[SEG][8];
+  unsigned in = 0;  // pixels of the piece that lie in the block
+  int tsum = 0;
+  {
+    int32_t tv[SEG][8];
+#pragma unroll
+    for (int s = 0; s < SEG; ++s) {
+      const int q = lb + s * LPB, row = q / PPR, col = 8 * (q % PPR);
+      if (fast) {
+        ld_words<2>(rs_base, ((y0 + row) * w + x0 + col) * 4, 0, tv[s]);
+      } else {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) tv[s][c] = ld_word(rs_base, min(y0 + row, h - 1) * w + min(x0 + col + c, w - 1));
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < SEG; ++s) {
+      const int q = lb + s * LPB, row = q / PPR, col = 8 * (q % PPR);
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const bool ok = row < nby && col + c < nbx;
+        in |= (unsigned)ok << (8 * s + c);
+        tsum += ok ? tv[s][c] : 0;
+        tp[s][c] = (double)tv[s][c];
+      }
+    }
+  }
+#pragma unroll 1
+  for (int dy = dy0; dy < D; dy += WPP) {
+    double rg[SEG][4 * NV];
+#pragma unroll
+    for (int s = 0; s < SEG; ++s)
+#pragma unroll
+      for (int c = 0; c < 4 * NV; ++c) rg[s][c] = (double)cur[s][c];
+    if (dy + WPP < D) load_region(dy + WPP);  // the next offset's row, under this one's sums
+    auto costs = [&](auto masked) __attribute__((always_inline)) {
+#pragma unroll
+      for (int dx = 0; dx < D; ++dx) {
+        double acc = 0.0;
+#pragma unroll
+        for (int s = 0; s < SEG; ++s)
+#pragma unroll
+          for (int c = 0; c < 8; ++c) {
+            double d = rg[s][dx + c] - tp[s][c];
+            if (decltype(masked)::value && !((in >> (8 * s + c)) & 1)) d = 0.0;
+            acc = fma(d, d, acc);
+          }
+        pw[RB::slot(dy * D + dx, lane)] = acc;
+      }
+    };
+    if (fast) costs(std::false_type{});
+    else costs(std::true_type{});
+  }
+  if (WPP > 1) {
+    __syncthreads();  // a workgroup is one pass
+    if (wave) return;
+  } else {
+    wave_sync();
+  }
+  // One candidate per lane of the block: its cost as 64 bits that order as
+  // the costs do (a non-negative float64's pattern, or the integer itself).
+  PKey best{~0ull, 0x7fffffff};
+  constexpr int kc = R * D + R;  // the candidate at the guess
+  unsigned long long cost_c = 0;
+  for (int k = lb; k < K; k += LPB) {
+    unsigned long long cost;
+    if (WIDE) {
+      cost = 0;
+#pragma unroll
+      for (int i = 0; i < LPB; ++i) cost += (unsigned long long)pw[RB::slot(k, RB::lane_of(blk, i))];
+    } else {
+      double sum = 0.0;
+#pragma unroll
+      for (int i = 0; i < LPB; ++i) sum += pw[RB::slot(k, RB::lane_of(blk, i))];
+      cost = (unsigned long long)__double_as_longlong(sum);
+    }
+    const int dyi = k / D, dxi = k - dyi * D;
+    const int dx = dxi - R, dy = dyi - R;
+    if (k == kc) cost_c = cost;
+    key_min(best, PKey{cost, ((dx * dx + dy * dy) << 16) | k});
+  }
+  const int from = RB::lane_of(blk, kc % LPB);
+  cost_c = ((unsigned long long)(unsigned)__shfl((int)(cost_c >> 32), from, 64) << 32) |
+           (unsigned)__shfl((int)(unsigned)(cost_c & 0xffffffffull), from, 64);
+  // minimum key and block sum over the block's lanes: every bit of the lane
+  // index but those that name the block
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) {
+    if (m >= PPR && m < BPW * PPR) continue;
+    PKey o;
+    o.ssd = ((unsigned long long)(unsigned)__shfl_xor((int)(best.ssd >> 32), m, 64) << 32) |
+            (unsigned)__shfl_xor((int)(unsigned)(best.ssd & 0xffffffffull), m, 64);
+    o.tie = __shfl_xor(best.tie, m, 64);
+    key_min(best, o);
+    tsum += __shfl_xor(tsum, m, 64);
+  }
+  bool keep = false;
+  if (ml.k12 > 0.0) {
+    const double gain = WIDE ? (double)(cost_c - best.ssd)
+                             : __longlong_as_double((long long)cost_c) - __longlong_as_double((long long)best.ssd);
+    keep = !gate_moves(ml, nby * nbx, tsum, gain);
+  }
+  if (valid && lb == 0) {
+    const int k = keep ? kc : best.tie & 0xffff;
+    const int dyi = k / D, dxi = k - dyi * D;
+    vecs[(long long)f * vstride + ml.voff + t] = make_int2(gx + dxi - R, gy + dyi - R);
   }
 }
 
@@ -370,14 +584,14 @@ __device__ __forceinline__ void halve(const double* in, double* out, int lane) {
   }
 }
 
-// Sums of 24 per-lane values over each group of LPG (16 or 64) lanes, written
+// Sums of 24 per-lane values over each group of LPG (16, 32 or 64) lanes, written
 // to tbl[0..24) of the group by one lane per value. Each partner step pairs
 // lanes of disjoint orbits, so after log2(LPG) steps every sum covers the
 // whole group. Every value is an integer below 2^53: the sums are exact in any
 // order.
 template <int LPG>
 __device__ __forceinline__ void group_sum24(const double* v, double* tbl, int lane, bool write) {
-  constexpr int TOP = LPG == 16 ? 3 : 5;
+  constexpr int TOP = LPG == 16 ? 3 : (LPG == 32 ? 4 : 5);
   double a[12], b[6], c[3];
   halve<TOP, 24>(v, a, lane);
   halve<TOP - 1, 12>(a, b, lane);
@@ -610,7 +824,269 @@ __global__ __launch_bounds__(256) void k_align_lk(const int32_t* __restrict__ py
   }
 }
 
+// Lucas-Kanade by columns, for tiles of 8, 16 or 32 half-res pixels (window
+// WIN = 16, 32 or 64): WIN lanes per tile, a lane walks down one window column
+// and reads the 3 x 3 frame neighbourhood and the base frame's row around it
+// straight from the level (one 12-byte load per row and frame, at a per-lane
+// offset plus a uniform row offset: no index arithmetic, no LDS copy), two
+// rows ahead of the sums. A wave's tiles belong to one frame. Where a window
+// or its displaced patch leaves the level, rows and columns are clamped (edge
+// replication) and lanes and rows past a clipped window add nothing.
+//
+// The sums, their order-free exactness and the iterations are those of
+// k_align_lk above, which stays for other tile sizes.
+//
+// Bound by the VALU (23 float64 multiply-adds and six conversions per row) and
+// the loads' latency at three waves per SIMD (152 VGPRs). Windows copied to
+// LDS by flat index took 2100 VALU instructions per wave and pass of four
+// tiles, 381 us at 12 MP x 8 and 28 us at 5 x 510 x 766 (32-pixel tiles); this
+// takes 1090, 260 and 22 us. Three one-word loads instead of one 12-byte load
+// per row, or neighbour columns from the adjacent lanes: 3 and 8 % slower
+// alignment; four rows ahead: registers spill (0.48 -> 0.67 ms).
+template <int WIN>
+__global__ __launch_bounds__(256, 3) void k_align_lk_cols(const int32_t* __restrict__ pyr,
+                                                          const int2* __restrict__ vecs, LkArgs a,
+                                                          float2* __restrict__ motion, int2* __restrict__ bm_out,
+                                                          int per_frame, int passes, int chunk) {
+  constexpr int TPW = 64 / WIN, RC = 2;  // tiles per wave; rows loaded together
+  __shared__ double tables[kWaves][TPW * 24];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int g = lane / WIN, l = lane % WIN;
+  double* tbl = tables[wave] + g * 24;
+  const int h = a.h, w = a.w, per = a.TY * a.TX;
+  const int gw = xcd_tile(blockIdx.x, gridDim.x) * (blockDim.x >> 6) + wave;
+  const int p0 = gw * chunk, p1 = min(passes, p0 + chunk);
+  const __amdgpu_buffer_rsrc_t rs_base = words_rsrc(pyr + (long long)a.ref * a.fstride, (long long)h * w);
+  // a pass's block-matching vectors are loaded one pass ahead
+  auto load_bm = [&](int p) {
+    const int f = p / per_frame, t = min((p - f * per_frame) * TPW + g, per - 1);
+    return f == a.ref ? make_int2(0, 0) : vecs[(long long)f * a.vstride + a.voff0 + t];
+  };
+  int2 next_bm = make_int2(0, 0);
+  if (p0 < p1) next_bm = load_bm(p0);
+  for (int p = p0; p < p1; ++p) {
+    const int f = p / per_frame;  // uniform
+    const int t0 = (p - f * per_frame) * TPW + g;
+    const bool valid = t0 < per;
+    const int t = valid ? t0 : per - 1;
+    const long long item = (long long)f * per + t;
+    const int2 bm = next_bm;
+    if (p + 1 < p1) next_bm = load_bm(p + 1);
+    if (f == a.ref) {
+      if (valid && l == 0) {
+        motion[item] = make_float2(0.f, 0.f);
+        if (bm_out) bm_out[item] = make_int2(0, 0);
+      }
+      continue;
+    }
+    const __amdgpu_buffer_rsrc_t rs = words_rsrc(pyr + (long long)f * a.fstride, (long long)h * w);
+    const int ty = t / a.TX, tx = t - ty * a.TX;
+    const int wy0 = max(0, ty * a.B - a.m), WH = min(ty * a.B + a.B + a.m, h) - wy0;
+    const int wx0 = max(0, tx * a.B - a.m), WW = min(tx * a.B + a.B + a.m, w) - wx0;
+    int ccx = bm.x, ccy = bm.y;  // centre of the 3 x 3 correlation offsets
+    const bool base_in = WH == WIN && WW == WIN && wy0 >= 1 && wx0 >= 1 && wy0 + WIN < h && wx0 + WIN < w;
+    double acc[24];
+    // partial sums of this lane's column, as tile_sums states them
+    auto sums = [&]() __attribute__((always_inline)) {
+      const int my = wy0 - 1 + ccy, mx = wx0 - 1 + ccx;  // the patch's first row and column
+      const bool in = base_in && my >= 0 && mx >= 0 && my + WIN + 1 < h && mx + WIN + 1 < w;
+      const bool fast = __all(in);
+      const int vb = ((wy0 - 1) * w + wx0 - 1 + l) * 4, vm = (my * w + mx + l) * 4;
+      int cb[3], cm[3];
+      if (!fast) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          cb[k] = clampi(wx0 - 1 + l + k, 0, w - 1);
+          cm[k] = clampi(mx + l + k, 0, w - 1);
+        }
+      }
+      // patch and base rows i .. i + N - 1 (0: the row above the window)
+      auto rows = [&](int i, auto& m, auto& b) __attribute__((always_inline)) {
+        constexpr int N = sizeof(m) / sizeof(m[0]);
+        if (fast) {
+#pragma unroll
+          for (int q = 0; q < N; ++q) {
+            const auto u = __builtin_amdgcn_raw_buffer_load_b96(rs, vm, (i + q) * w * 4, 0);
+            const auto v = __builtin_amdgcn_raw_buffer_load_b96(rs_base, vb, (i + q) * w * 4, 0);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+              m[q][k] = (int)u[k];
+              b[q][k] = (int)v[k];
+            }
+          }
+        } else {
+#pragma unroll
+          for (int q = 0; q < N; ++q) {
+            const int ym = clampi(my + i + q, 0, h - 1) * w, yb = clampi(wy0 - 1 + i + q, 0, h - 1) * w;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+              m[q][k] = ld_word(rs, ym + cm[k]);
+              b[q][k] = ld_word(rs_base, yb + cb[k]);
+            }
+          }
+        }
+      };
+#pragma unroll
+      for (int i = 0; i < 24; ++i) acc[i] = 0.0;
+      int m01[2][3], b01[2][3], mn[RC][3], bn[RC][3];
+      rows(0, m01, b01);
+      rows(2, mn, bn);
+      double ra[3], rb[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        ra[k] = (double)m01[0][k];
+        rb[k] = (double)m01[1][k];
+      }
+      int bu = b01[0][1], bc[3] = {b01[1][0], b01[1][1], b01[1][2]};
+#pragma unroll 1
+      for (int r0 = 0; r0 < WIN; r0 += 2 * RC) {
+        // window rows r0 .. r0 + RC - 1 from mn, bn; the rows after them in flight
+        int m2[RC][3], b2[RC][3];
+        auto step = [&](int r, const int (&m)[3], const int (&b)[3]) __attribute__((always_inline)) {
+          double rc[3];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) rc[k] = (double)m[k];
+          int dxi = bc[2] - bc[0], dyi = b[1] - bu;
+          if (!fast && (l >= WW || r >= WH)) dxi = dyi = 0;
+          const double dx = (double)dxi, dy = (double)dyi, tv = (double)bc[1];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            acc[k] = fma(dx, ra[k], acc[k]);
+            acc[3 + k] = fma(dx, rb[k], acc[3 + k]);
+            acc[6 + k] = fma(dx, rc[k], acc[6 + k]);
+            acc[9 + k] = fma(dy, ra[k], acc[9 + k]);
+            acc[12 + k] = fma(dy, rb[k], acc[12 + k]);
+            acc[15 + k] = fma(dy, rc[k], acc[15 + k]);
+          }
+          acc[18] = fma(dx, tv, acc[18]);
+          acc[19] = fma(dy, tv, acc[19]);
+          acc[20] = fma(dx, dx, acc[20]);
+          acc[21] = fma(dx, dy, acc[21]);
+          acc[22] = fma(dy, dy, acc[22]);
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            ra[k] = rb[k];
+            rb[k] = rc[k];
+          }
+          bu = bc[1];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) bc[k] = b[k];
+        };
+        rows(r0 + RC + 2, m2, b2);
+#pragma unroll
+        for (int q = 0; q < RC; ++q) step(r0 + q, mn[q], bn[q]);
+        if (r0 + 2 * RC < WIN) rows(r0 + 2 * RC + 2, mn, bn);
+#pragma unroll
+        for (int q = 0; q < RC; ++q) step(r0 + RC + q, m2[q], b2[q]);
+      }
+    };
+    double k2 = 0.0;
+    bool ok = false;
+    double vx = bm.x, vy = bm.y;
+#pragma unroll 1
+    for (int it = 0; it < a.iters; ++it) {
+      const double fxf = floor(vx), fyf = floor(vy);
+      // the first sums, or the sample cell left the correlated offsets:
+      // re-centre those tiles (the others' sums are formed again and dropped)
+      const bool need = it == 0 || (ok && (fxf < ccx - 1 || fxf > ccx || fyf < ccy - 1 || fyf > ccy));
+      if (__any(need)) {
+        if (need) {
+          ccx = (int)fmax(fmin(fxf, 1e9), -1e9);
+          ccy = (int)fmax(fmin(fyf, 1e9), -1e9);
+        }
+        wave_sync();
+        sums();
+        group_sum24<WIN>(acc, tbl, lane, need);
+        wave_sync();
+      }
+      // (every round of sums writes the same base-frame sums)
+      const double Hxx = tbl[20], Hxy = tbl[21], Hyy = tbl[22], STx = tbl[18], STy = tbl[19];
+      if (it == 0) {
+        // Singular-window test on the exact sums, rounded step by step as
+        // written (no fused multiply-add), so that it is decided identically
+        // everywhere.
+        const double tr = __dadd_rn(Hxx, Hyy);
+        const double det = __dsub_rn(__dmul_rn(Hxx, Hyy), __dmul_rn(Hxy, Hxy));
+        const double thr = __dmul_rn(__dmul_rn(1e-9, tr), tr);
+        ok = valid && tr > 0.0 && det > thr;
+        k2 = ok ? 2.0 / det : 0.0;  // H and b here are 4x and 2x the half-gradient ones
+      }
+      if (ok) {
+        const double fx = vx - fxf, fy = vy - fyf;
+        const int o00 = ((int)(fyf - ccy) + 1) * 3 + (int)(fxf - ccx) + 1;
+        const double w00 = (1.0 - fx) * (1.0 - fy), w01 = fx * (1.0 - fy), w10 = (1.0 - fx) * fy, w11 = fx * fy;
+        const double sx = w00 * tbl[o00] + w01 * tbl[o00 + 1] + w10 * tbl[o00 + 3] + w11 * tbl[o00 + 4] - STx;
+        const double sy =
+            w00 * tbl[9 + o00] + w01 * tbl[9 + o00 + 1] + w10 * tbl[9 + o00 + 3] + w11 * tbl[9 + o00 + 4] - STy;
+        vx -= k2 * (Hyy * sx - Hxy * sy);
+        vy -= k2 * (Hxx * sy - Hxy * sx);
+      }
+    }
+    if (valid && l == 0) {
+      motion[item] = make_float2((float)(2.0 * vx), (float)(2.0 * vy));
+      if (bm_out) bm_out[item] = bm;
+    }
+    wave_sync();  // the next tiles overwrite this wave's tables
+  }
+}
+
+template <int WIN>
+hipError_t lk_cols(const int32_t* pyr, const int2* vecs, const LkArgs& a, int n, int cus, float* motion,
+                   int* block_match, hipStream_t stream) {
+  constexpr int TPW = 64 / WIN;
+  const int per_frame = (a.TY * a.TX + TPW - 1) / TPW;
+  const long long passes = (long long)n * per_frame;
+  // about eight rounds of the resident waves (three per SIMD), so that runs of
+  // tiles with far-apart vectors, whose loads miss the caches, even out (one
+  // round: 12 MP x 8 alignment 0.57 ms, eight 0.48 ms, one pass per wave 0.50)
+  const long long waves_wanted = (long long)cus * 12 * 8;
+  const long long chunk = (passes + waves_wanted - 1) / waves_wanted;
+  const int waves = passes >= 4ll * cus ? kWaves : 1;  // few passes spread over more compute units
+  const unsigned groups = (unsigned)(((passes + chunk - 1) / chunk + waves - 1) / waves);
+  hipLaunchKernelGGL(k_align_lk_cols<WIN>, dim3(groups), dim3(64 * waves), 0, stream, pyr, vecs, a, (float2*)motion,
+                     (int2*)block_match, per_frame, (int)passes, (int)chunk);
+  return hipGetLastError();
+}
+
 unsigned cdiv(long long a, long long b) { return (unsigned)((a + b - 1) / b); }
+
+template <int B, int R, bool WIDE>
+hipError_t match_rows(const int32_t* pyr, int2* vecs, const MatchLevel& ml, const AlignGeom& ag, int cus,
+                      hipStream_t stream) {
+  constexpr int K = (2 * R + 1) * (2 * R + 1), BPW = RowBlocks<B>::BPW;
+  const int per_frame = (ml.gby * ml.gbx + BPW - 1) / BPW;
+  const long long passes = (long long)(ag.n - 1) * per_frame;
+  // Radius 2: a wave takes one pass (kept persistent, each wave's share of
+  // consecutive passes ran up to twice as long as another's: 12 MP x 8 level 0
+  // 129 us instead of 100); four per workgroup where that still fills the
+  // device, else one, so that few passes spread over more compute units.
+  // Radius 4 is the coarsest level's, which has few blocks: four waves share a
+  // pass (one wave each took 16-22 us at 510 x 766 x 5 and at 12 MP x 8).
+  constexpr int WPP = R == 2 ? 1 : 4;
+  const int waves = WPP > 1 ? WPP : (passes >= 4ll * cus ? 4 : 1), per_group = waves / WPP;
+  const unsigned groups = (unsigned)((passes + per_group - 1) / per_group);
+  hipLaunchKernelGGL((k_align_match_rows<B, R, WIDE, WPP>), dim3(groups), dim3(64 * waves),
+                     (size_t)per_group * K * 64 * 8, stream, pyr, vecs, ml, ag.ref, ag.fstride, ag.vstride, per_frame,
+                     (int)passes);
+  return hipGetLastError();
+}
+
+// Block matching of one level by rows where that form exists (see
+// k_align_match_rows); false: the general kernel takes the level.
+bool launch_match_rows(const int32_t* pyr, int2* vecs, const MatchLevel& ml, const AlignGeom& ag, int cus,
+                       hipStream_t stream, hipError_t* err) {
+  if ((long long)ml.h * ml.w >= (1ll << 29)) return false;  // byte offsets are int
+  const bool wide = ml.level == 3;
+  if (ml.level > 3 || (wide && ml.B != 8)) return false;
+  if (ml.R == 2 && ml.B == 8 && !wide) *err = match_rows<8, 2, false>(pyr, vecs, ml, ag, cus, stream);
+  else if (ml.R == 2 && ml.B == 8) *err = match_rows<8, 2, true>(pyr, vecs, ml, ag, cus, stream);
+  else if (ml.R == 2 && ml.B == 16) *err = match_rows<16, 2, false>(pyr, vecs, ml, ag, cus, stream);
+  else if (ml.R == 2 && ml.B == 32) *err = match_rows<32, 2, false>(pyr, vecs, ml, ag, cus, stream);
+  else if (ml.R == 4 && ml.B == 8 && !wide) *err = match_rows<8, 4, false>(pyr, vecs, ml, ag, cus, stream);
+  else if (ml.R == 4 && ml.B == 8) *err = match_rows<8, 4, true>(pyr, vecs, ml, ag, cus, stream);
+  else return false;
+  return true;
+}
 
 }  // namespace
 
@@ -653,6 +1129,10 @@ hipError_t launch_align(const AlignGeom& ag, const uint16_t* frames, int H, int 
       ml.nb = ag.nb;
       ml.black = ag.black;
       ml.rng = ag.rng;
+      if (launch_match_rows(pyr, vecs, ml, ag, cus, stream, &err)) {
+        if (err != hipSuccess) return err;
+        continue;
+      }
       const int E = ml.B + 2 * ml.R;
       const int waves = ml.B <= 8 ? kWaves : 1;  // keeps LDS within 64 KiB per workgroup
       const size_t lds = (size_t)waves * 4 * (ml.B * ml.B + E * E) * 4;
@@ -683,6 +1163,9 @@ hipError_t launch_align(const AlignGeom& ag, const uint16_t* frames, int H, int 
   a.fstride = ag.fstride;
   a.vstride = ag.vstride;
   a.voff0 = ag.voff[0];
+  if (a.B == 8) return lk_cols<16>(pyr, vecs, a, ag.n, cus, motion, block_match, stream);
+  if (a.B == 16) return lk_cols<32>(pyr, vecs, a, ag.n, cus, motion, block_match, stream);
+  if (a.B == 32) return lk_cols<64>(pyr, vecs, a, ag.n, cus, motion, block_match, stream);
   const int sw = ((a.B + 2 * a.m + 2) + 1) & ~1;  // window edge with its border, at most; even
   const long long items = (long long)ag.n * a.TY * a.TX;
   const int lpg = a.B <= 8 ? 16 : 64;
