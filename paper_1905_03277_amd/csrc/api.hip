@@ -403,6 +403,7 @@ hmfsr_status hmfsr_merge_backward(const hmfsr_desc* desc, const hmfsr_tuning* tu
   bc.kn = tuning->k_denoise;
   bc.kst = tuning->k_stretch;
   bc.ksh = tuning->k_shrink;
+  bc.iksh = 1.0 / (double)tuning->k_shrink;
   bc.sl = mc.om.inv_16_range_dtr / (double)tuning->d_tr;
   bc.tiles_x = (g.OW + 63) / 64;
   bc.tiles_y = (g.OH + kBwdRows - 1) / kBwdRows;

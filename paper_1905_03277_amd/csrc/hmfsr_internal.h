@@ -154,6 +154,7 @@ constexpr int kBwdRH = (64 / 2 + 2) * (kBwdRows / 2 + 2);   // R_hat window cell
 
 struct BwdConsts {
   double kd, kn, kst, ksh;  // k_detail, k_denoise, k_stretch, k_shrink
+  double iksh;              // 1 / k_shrink
   double sl;                // dD/dD_tr per unit of sqrt(lambda1) of the integer tensor
   int tiles_x, tiles_y, n_tiles;  // output tiles of the adjoint's tile shape
 };

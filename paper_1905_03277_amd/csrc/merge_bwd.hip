@@ -52,9 +52,17 @@ constexpr int BWAVES = BTHREADS / 64;
 constexpr int BPX = BMH / BWAVES;  // pixel rows per thread
 using BCP = Caps<BMH>;
 static_assert(BCP::VT == kBwdVT && BCP::RH == kBwdRH, "partial layouts follow the tile caps");
-static_assert(BCP::VT <= BTHREADS, "one alignment tile per thread at most");
+static_assert(BCP::RAW == 4 * BCP::LUMA, "the raw window is the luma window's quads");
+constexpr int BNV = 2 * BCP::VT;                                        // displacements staged at once
+constexpr int BQB = (BCP::LUMA + BTHREADS - 1) / BTHREADS;               // quads per thread
+constexpr int BRHT = (BCP::RH + BTHREADS - 1) / BTHREADS;                // R_hat entries per thread
 
 struct BwdSmem {
+  // the windows first: their addresses then fit the instructions' offsets
+  float2 sRaw[BCP::RAW / 2];
+  double sOm[3][BCP::OM];
+  float sLum[BCP::LUMA];
+  float sRh[BCP::RH];
   double sX[MW], sY[BMH];
   int sTyRow[BMH], sTxCol[MW];
   int sRlo[BCP::TY], sRhi[BCP::TY], sClo[BCP::TX], sChi[BCP::TX];
@@ -63,25 +71,20 @@ struct BwdSmem {
   int sRxa[MW], sRxb[MW];             // R_hat window columns of each pixel column
   float sRfx[MW];
   int sIlo[BCP::RH_H], sIhi[BCP::RH_H];  // pixel rows touching each window row
-  float2 sV[BCP::VT];
-  Bounds sTB[BCP::VT];
-  float sRaw[BCP::RAW];
-  float sLum[BCP::LUMA];
-  double sOm[3][BCP::OM];
+  float2 sV[BNV];     // displacement per frame slot and alignment tile (slot * ntiles + tile)
+  int sBox[FCH][8];  // footprint of the whole tile per frame slot: Bounds, upper ends negated
   // dOmega/dtheta per half-res pixel: the gradient direction as (cos 2phi,
   // sin 2phi) in float64 (the edge projection of dL/dOmega cancels up to
   // (k1/k2)^2), and the per-scalar factors p0..p9.
   double2 sDir[BCP::OM];
   float4 sP[2][BCP::OM];
   float2 sP2[BCP::OM];
-  float sRh[BCP::RH];
-  // per frame slot (frame index & 1): a frame's sums are added up during the next frame
-  double2 sHm[2][BMH][BCP::TX];  // per pixel row and alignment tile column: sum of dL/dp
-  float sHa[2][BMH][BCP::RH_W];  // per pixel row and R_hat column: dL/drho through the left corners
-  float sHb[2][BMH][BCP::RH_W];  // ... through the right corners
+  // a frame's sums are added up during the next frame's staging
+  double2 sHm[BMH][BCP::TX];  // per pixel row and alignment tile column: sum of dL/dp
+  float sHa[BMH][BCP::RH_W];  // per pixel row and R_hat column: dL/drho through the left corners
+  float sHb[BMH][BCP::RH_W];  // ... through the right corners
   int sRun[MW];  // per lane: first lane of its runs (alignment tile, left and right R_hat corner column)
   double sAcc[BWAVES][6];
-  int sRed[8];
   int sRh0[4];
 };
 
@@ -144,13 +147,20 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;  // lane 0 holds the sum, always added in the same order
 }
 
+// Bound by the VALU (about 690 instructions per wave of 64 output pixels and
+// frame, some 180 of them float64) and, at three waves per SIMD (168 VGPRs,
+// 48 KB of LDS per workgroup), by latency: the Omega pass occupies half the
+// waves at scale 2. Quads, staged footprints, loads under the row sums and
+// colours from two parities as in the forward, and three barriers per frame
+// instead of six: 701 -> 609 us for 8 x 768 x 1024 at scale 2, 50 -> 32 us for
+// 4 x 188 x 252 at 1.25.
 __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
     const uint16_t* __restrict__ frames, const float* __restrict__ motion,
     const float* __restrict__ rmin, const float* __restrict__ saved,
     const float* __restrict__ grad_out, Geometry g, MergeConsts mc, BwdConsts bc,
     double* __restrict__ part_theta, double* __restrict__ part_mo, float* __restrict__ part_rh) {
   __shared__ BwdSmem sm;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tile = xcd_tile(blockIdx.x, bc.n_tiles);
   const int tile_x = tile % bc.tiles_x, tile_y = tile / bc.tiles_x;
   const int C0 = tile_x * MW, R0 = tile_y * BMH;
@@ -170,8 +180,10 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
     sm.sTyRow[r] = r < nrow ? tile_of(Y, g.T, g.TY) : 0;
   }
   __syncthreads();
-  const int txA = sm.sTxCol[0], txB = sm.sTxCol[ncol - 1];
-  const int tyA = sm.sTyRow[0], tyB = sm.sTyRow[nrow - 1];
+  const int txA = __builtin_amdgcn_readfirstlane(sm.sTxCol[0]);
+  const int txB = __builtin_amdgcn_readfirstlane(sm.sTxCol[ncol - 1]);
+  const int tyA = __builtin_amdgcn_readfirstlane(sm.sTyRow[0]);
+  const int tyB = __builtin_amdgcn_readfirstlane(sm.sTyRow[nrow - 1]);
   const int ntx = txB - txA + 1, nty = tyB - tyA + 1, ntiles = ntx * nty;
   if (tid < ncol) {
     const int t = sm.sTxCol[tid] - txA;
@@ -188,8 +200,10 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
     rh_range(R0, R0 + nrow - 1, g.scale, g.h, sm.sRh0[2], sm.sRh0[3]);
   }
   __syncthreads();
-  const int rhc0 = sm.sRh0[0], rhw = sm.sRh0[1] - sm.sRh0[0] + 1;
-  const int rhr0 = sm.sRh0[2], rhh = sm.sRh0[3] - sm.sRh0[2] + 1;
+  const int rhc0 = __builtin_amdgcn_readfirstlane(sm.sRh0[0]);
+  const int rhw = __builtin_amdgcn_readfirstlane(sm.sRh0[1]) - rhc0 + 1;
+  const int rhr0 = __builtin_amdgcn_readfirstlane(sm.sRh0[2]);
+  const int rhh = __builtin_amdgcn_readfirstlane(sm.sRh0[3]) - rhr0 + 1;
   for (int r = tid; r < BMH; r += BTHREADS) {
     const double hy = sm.sY[r] * 0.5 - 0.5;
     const double fhy = floor(hy);
@@ -285,20 +299,19 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
   }
   double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
 
-  // Over the tile's pixel rows, in fixed order, the per-row sums a frame left
-  // in slot `slot`: dL/dp per alignment tile and dL/drho onto the tile's R_hat
-  // window, into frame m's per-workgroup partials. Runs after the barrier
-  // that opens the next frame (or follows the last), beside that frame's
-  // first loads.
-  auto add_rows = [&](int slot, int m) {
+  // Over the tile's pixel rows, in fixed order, the per-row sums frame m left:
+  // dL/dp per alignment tile and dL/drho onto the tile's R_hat window, into
+  // its per-workgroup partials. Runs after the barrier that opens the next
+  // frame (or follows the last), beside that frame's staging.
+  auto add_rows = [&](int m) {
     const int nwin = rhh * rhw;
-    for (int k = tid; k < ntiles + nwin; k += BTHREADS) {
+    for (int k = here(tid); k < ntiles + nwin; k += BTHREADS) {
       if (k < ntiles) {
         const int ky = k / ntx, kx = k - ky * ntx;
         double sx = 0.0, sy = 0.0;
         for (int r = sm.sRlo[ky]; r <= sm.sRhi[ky]; ++r) {
-          sx += sm.sHm[slot][r][kx].x;
-          sy += sm.sHm[slot][r][kx].y;
+          sx += sm.sHm[r][kx].x;
+          sy += sm.sHm[r][kx].y;
         }
         double* dst = part_mo + (((size_t)tile * g.n + m) * kBwdVT + k) * 2;
         dst[0] = sx;
@@ -310,7 +323,7 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
         for (int r = sm.sIlo[I]; r <= sm.sIhi[I]; ++r) {
           const float fyr = sm.sRow[r].fy;
           const float wgt = (sm.sRya[r] == I ? 1.f - fyr : 0.f) + (sm.sRyb[r] == I ? fyr : 0.f);
-          s = fmaf(wgt, sm.sHa[slot][r][J] + sm.sHb[slot][r][J], s);
+          s = fmaf(wgt, sm.sHa[r][J] + sm.sHb[r][J], s);
         }
         part_rh[((size_t)m * bc.n_tiles + tile) * kBwdRH + q] = s;
       }
@@ -318,345 +331,393 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
   };
   auto frame_of = [&](int fi) { return fi == 0 ? g.ref : (fi <= g.ref ? fi - 1 : fi); };
 
-  for (int fi = 0; fi < g.n; ++fi) {
-    const int n = fi == 0 ? g.ref : (fi <= g.ref ? fi - 1 : fi);
-    const bool is_ref = n == g.ref;
-    const uint16_t* f = frames + (size_t)n * g.H * g.W;
-    __syncthreads();
-    // this thread's alignment tile (at most one: ntiles <= VT <= BTHREADS):
-    // its displacement loads in flight together with the R_hat window's
-    float2 v = make_float2(0.f, 0.f);
-    if (tid < ntiles && !is_ref) {
-      const int ky = tid / ntx;
-      const float* p = motion + (((size_t)n * g.TY + tyA + ky) * g.TX + txA + (tid - ky * ntx)) * 2;
-      v = make_float2(p[0], p[1]);
-    }
-    if (tid < 8) sm.sRed[tid] = 0x7fffffff;
-    // every load of the R_hat window in flight before its stores (entries
-    // past the window re-read its last one and are not stored); the previous
-    // frame's row sums are added up while they are
-    constexpr int RHT = (BCP::RH + BTHREADS - 1) / BTHREADS;
+  // The R_hat window's entries of this thread: byte offsets in a frame's map
+  // (entries past the window re-read its last one and are not stored).
+  int rho_off[BRHT];
+  {
+    const float inv = window_inv(rhw);
     const int nrh = rhw * rhh;
-    float rhv[RHT];
-    if (!is_ref) {
-      const float* rm = rmin + (size_t)n * g.h * g.w;
-      const float inv = 1.f / (float)rhw;
 #pragma unroll
-      for (int i = 0; i < RHT; ++i) {
-        const int k = min(tid + i * BTHREADS, nrh - 1);
-        const int r = split_row(k, inv);
-        rhv[i] = rm[(unsigned)((rhr0 + r) * g.w + rhc0 + k - r * rhw)];  // below 2^28
-      }
-    }
-    if (fi >= 2) add_rows((fi - 1) & 1, frame_of(fi - 1));  // frame 0 is the base frame: no sums
-    if (!is_ref) {
-#pragma unroll
-      for (int i = 0; i < RHT; ++i)
-        if (tid + i * BTHREADS < nrh) sm.sRh[tid + i * BTHREADS] = rhv[i];
-    }
-    // clamping keeps non-finite or huge vectors finite and changes no result
-    if (tid < ntiles) sm.sV[tid] = make_float2(fminf(fmaxf(v.x, -vlim), vlim), fminf(fmaxf(v.y, -vlim), vlim));
-    // this frame's dL/drho and dL/dp of the thread's pixels (0 where skipped)
-    float pgr[BPX], pgx[BPX], pgy[BPX];
-#pragma unroll
-    for (int p = 0; p < BPX; ++p) pgr[p] = pgx[p] = pgy[p] = 0.f;
-    __syncthreads();
-    for (int k = tid; k < ntiles; k += BTHREADS) {
-      const int ky = k / ntx, kx = k - ky * ntx;
-      const float2 v = sm.sV[k];
-      const Bounds b = footprint(sm.sX[sm.sClo[kx]] + (double)v.x, sm.sX[sm.sChi[kx]] + (double)v.x,
-                                 sm.sY[sm.sRlo[ky]] + (double)v.y, sm.sY[sm.sRhi[ky]] + (double)v.y, g);
-      sm.sTB[k] = b;
-      atomicMin(&sm.sRed[0], b.jc0); atomicMin(&sm.sRed[1], -b.jc1);
-      atomicMin(&sm.sRed[2], b.ic0); atomicMin(&sm.sRed[3], -b.ic1);
-      atomicMin(&sm.sRed[4], b.hj0); atomicMin(&sm.sRed[5], -b.hj1);
-      atomicMin(&sm.sRed[6], b.hi0); atomicMin(&sm.sRed[7], -b.hi1);
-    }
-    __syncthreads();
-
-    bool whole = true;
-    int seg = 0;
-    while (true) {
-      Bounds bd;
-      if (whole) {
-        bd.jc0 = sm.sRed[0]; bd.jc1 = -sm.sRed[1]; bd.ic0 = sm.sRed[2]; bd.ic1 = -sm.sRed[3];
-        bd.hj0 = sm.sRed[4]; bd.hj1 = -sm.sRed[5]; bd.hi0 = sm.sRed[6]; bd.hi1 = -sm.sRed[7];
-      } else {
-        bd = sm.sTB[seg];
-      }
-      const int sty = whole ? -1 : seg / ntx, stx = whole ? -1 : seg % ntx;
-      // the forward's windows (one alignment tile's always fit: its footprint
-      // stops at the frame's ring)
-      const Win wn = make_win(bd, g);
-      const int oc0 = wn.oc0, ow = wn.ow, or0 = wn.or0, oh = wn.oh;
-      const int lc0 = wn.lc0, lr0 = wn.lr0, lw = wn.lw, lh = wn.lh;
-      const int rc0 = wn.rc0, rr0 = wn.rr0, rw = wn.rw, rh = wn.rh;
-      if (whole && (ow * oh > BCP::OM || lw * lh > BCP::LUMA || rw * rh > BCP::RAW)) {
-        whole = false;
-        seg = 0;
-        continue;
-      }
-      {
-        // loads in batches of four in flight before their stores: each reads
-        // the clamped position and the zero outside the frame is chosen after
-        constexpr int RB = 4;
-        const float inv = 1.f / (float)rw;
-        const int nr = rw * rh;
-        for (int k0 = tid; k0 < nr; k0 += RB * BTHREADS) {
-          uint32_t rv[RB];
-          bool rin[RB];
-#pragma unroll
-          for (int i = 0; i < RB; ++i) {
-            const int k = min(k0 + i * BTHREADS, nr - 1);
-            const int r = split_row(k, inv), c = k - r * rw;
-            const int gr = rr0 + r, gc = rc0 + c;
-            rin[i] = gr >= 0 && gr < g.H && gc >= 0 && gc < g.W;
-            rv[i] = f[(unsigned)(clampi(gr, 0, g.H - 1) * g.W + clampi(gc, 0, g.W - 1))];  // below 2^30
-          }
-#pragma unroll
-          for (int i = 0; i < RB; ++i) {
-            const int k = k0 + i * BTHREADS;
-            if (k < nr) sm.sRaw[k] = rin[i] ? (float)rv[i] : 0.f;
-          }
-        }
-      }
-      __syncthreads();
-      {
-        const float inv = 1.f / (float)lw;
-        for (int k = tid; k < lw * lh; k += BTHREADS) {
-          const int r = split_row(k, inv), c = k - r * lw;
-          const int o = (2 * clampi(lr0 + r, 0, g.h - 1) - rr0) * rw + 2 * clampi(lc0 + c, 0, g.w - 1) - rc0;
-          sm.sLum[k] = (sm.sRaw[o] + sm.sRaw[o + 1]) + (sm.sRaw[o + rw] + sm.sRaw[o + rw + 1]);
-        }
-      }
-      __syncthreads();
-      {
-        const float inv = 1.f / (float)ow;
-        for (int k = tid; k < ow * oh; k += BTHREADS) {
-          const int r = split_row(k, inv), c = k - r * ow;
-          const int I = clampi(or0 + r, 0, g.h - 1), J = clampi(oc0 + c, 0, g.w - 1);
-          const int base = (I - 1 - lr0) * lw + (J - 1 - lc0);  // the window's ring repeats the edges
-          float l[3][3];
-#pragma unroll
-          for (int a = 0; a < 3; ++a)
-#pragma unroll
-            for (int bb = 0; bb < 3; ++bb) l[a][bb] = sm.sLum[base + a * lw + bb];
-          double oxx, oxy, oyy;
-          OmegaParts pt;
-          omega_parts_from_quads(l, mc.om, oxx, oxy, oyy, pt);
-          sm.sOm[0][k] = oxx;
-          sm.sOm[1][k] = oxy;
-          sm.sOm[2][k] = oyy;
-          // sigma_1,2 = k1s, k2s (k1 = sigma_1^2): per unit dL/dk1, dL/dk2 the
-          // derivatives of sigma_1,2 in every scalar, each times 2 sigma.
-          const double D = pt.D, A = pt.A, invA = pt.invA;
-          const double s1 = 2.0 * pt.k1s, s2 = 2.0 * pt.k2s;
-          const double f1 = pt.d_free ? s1 * (bc.kn - bc.kst * A) : 0.0;
-          const double f2 = pt.d_free ? s2 * (bc.kn - invA / bc.ksh) : 0.0;
-          const double sl = pt.sqrt_l1 * bc.sl;
-          sm.sDir[k] = make_double2(pt.c2, pt.s2);
-          sm.sP[0][k] = make_float4((float)(s1 * pt.k1s), (float)(s2 * pt.k2s), (float)(s1 * D), (float)(s2 * D));
-          sm.sP[1][k] = make_float4((float)(s1 * (1.0 - D) * A), (float)(s2 * (1.0 - D) * invA), (float)f1,
-                                    (float)f2);
-          sm.sP2[k] = make_float2((float)(f1 * sl), (float)(f2 * sl));
-        }
-      }
-      __syncthreads();
-
-      if (col_ok) {
-#pragma unroll
-        for (int p = 0; p < BPX; ++p) {
-          const int r = wave * BPX + p;
-          if (r >= nrow) continue;
-          const int tyl = sm.sTyRow[r] - tyA;
-          if (!whole && (tyl != sty || txl != stx)) continue;
-          float rho = 1.f;
-          if (!is_ref) {
-            const RowInfo ri = sm.sRow[r];
-            const float top = sm.sRh[ri.ya + rxa] + rfx * (sm.sRh[ri.ya + rxb] - sm.sRh[ri.ya + rxa]);
-            const float bot = sm.sRh[ri.yb + rxa] + rfx * (sm.sRh[ri.yb + rxb] - sm.sRh[ri.yb + rxa]);
-            rho = top + ri.fy * (bot - top);
-            if (!(rho > 0.f)) continue;
-          }
-          const float2 v = sm.sV[tyl * ntx + txl];
-          const double px = X + (double)v.x, py = sm.sY[r] + (double)v.y;
-          const double fjc = floor(px), fic = floor(py);
-          const double frx = px - fjc, fry = py - fic;
-          const int jc = (int)fjc, ic = (int)fic;
-          if (samples_outside(jc, ic, g)) continue;  // no in-frame sample: no term, no gradient
-          const double hx = px * 0.5 - 0.5, hy = py * 0.5 - 0.5;
-          const double fhj = floor(hx), fhi = floor(hy);
-          const double fx = hx - fhj, fy = hy - fhi;
-          const int ob = ((int)fhi - or0) * ow + ((int)fhj - oc0);
-          double O[3], dOx[3], dOy[3];  // Omega_bar and its derivatives along hx, hy
-#pragma unroll
-          for (int e = 0; e < 3; ++e) {
-            const double o00 = sm.sOm[e][ob], o01 = sm.sOm[e][ob + 1];
-            const double o10 = sm.sOm[e][ob + ow], o11 = sm.sOm[e][ob + ow + 1];
-            const double top = fma(fx, o01 - o00, o00);
-            const double bot = fma(fx, o11 - o10, o10);
-            O[e] = fma(fy, bot - top, top);
-            dOx[e] = fma(fy, (o11 - o10) - (o01 - o00), o01 - o00);
-            dOy[e] = bot - top;
-          }
-          const double idet = recip64_1(O[0] * O[2] - O[1] * O[1]);
-          const double sc = NEG_HALF_LOG2E * idet;
-          const double qa = O[2] * sc, qb2 = -2.0 * O[1] * sc, qc = O[0] * sc;
-          double dx[3], dy[3];
-          float dxf[3], dyf[3];  // offsets of in-frame samples, 0 elsewhere
-#pragma unroll
-          for (int j = 0; j < 3; ++j) {
-            dx[j] = ((double)j - 0.5) - frx;
-            dy[j] = ((double)j - 0.5) - fry;
-            const int qj = jc + j - 1, qi = ic + j - 1;
-            const bool okx = qj >= 0 && qj < g.W, oky = qi >= 0 && qi < g.H;
-            dxf[j] = okx ? (float)dx[j] : 0.f;
-            dyf[j] = oky ? (float)dy[j] : 0.f;
-            if (!okx) dx[j] = FAR_X;
-            if (!oky) dy[j] = FAR_Y;
-          }
-          double E[3][3];
-          {
-            double ax[3], cy[3], by[3];
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-              ax[j] = qa * (dx[j] * dx[j]);
-              cy[j] = qc * (dy[j] * dy[j]);
-              by[j] = qb2 * dy[j];
-            }
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-              for (int j = 0; j < 3; ++j) E[i][j] = fma(by[i], dx[j], ax[j] + cy[i]);
-          }
-          // channel of each colour group: centre (0), left/right (1), up/down (2), corners (3)
-          const int pr = ic & 1, pc = jc & 1;
-          const int c0 = colour_of(mc.col4, pr * 2 + pc);
-          const int c1 = colour_of(mc.col4, pr * 2 + (pc ^ 1));
-          const bool isG = c0 == 1;
-          const bool xIsR = (isG ? c1 : c0) == 0;  // group "X" (centre or left/right) is red
-          float Mg[4], Gg[4], Ch[4], Cl[4];
-          route4(mref[p], isG, xIsR, Mg);
-          route4(gam[p], isG, xIsR, Gg);
-          route4(chi[p], isG, xIsR, Ch);
-          route4(clo[p], isG, xIsR, Cl);
-          const int vb = (ic - 1 - rr0) * rw + (jc - 1 - rc0);
-          float a[3][3];
-          float grho = 0.f;
-#pragma unroll
-          for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-              const int q = (i == 1 && j == 1) ? 0 : (i == 1 ? 1 : (j == 1 ? 2 : 3));
-              const float w = __builtin_amdgcn_exp2f((float)(E[i][j] - (double)Mg[q]));
-              const float bq = Gg[q] * w * ((sm.sRaw[vb + i * rw + j] - Ch[q]) - Cl[q]);  // dL/drho part
-              grho += bq;
-              a[i][j] = rho * bq;  // dL/de
-            }
-          // S = sum a d d^T, t = sum a d (offsets separate into columns and rows)
-          float Acol[3], Arow[3], Sxy = 0.f;
-#pragma unroll
-          for (int j = 0; j < 3; ++j) Acol[j] = a[0][j] + a[1][j] + a[2][j];
-#pragma unroll
-          for (int i = 0; i < 3; ++i) {
-            Arow[i] = a[i][0] + a[i][1] + a[i][2];
-            Sxy = fmaf(dyf[i], fmaf(a[i][0], dxf[0], fmaf(a[i][1], dxf[1], a[i][2] * dxf[2])), Sxy);
-          }
-          float Sxx = 0.f, Syy = 0.f, tx = 0.f, ty = 0.f;
-#pragma unroll
-          for (int j = 0; j < 3; ++j) {
-            tx = fmaf(Acol[j], dxf[j], tx);
-            Sxx = fmaf(Acol[j] * dxf[j], dxf[j], Sxx);
-            ty = fmaf(Arow[j], dyf[j], ty);
-            Syy = fmaf(Arow[j] * dyf[j], dyf[j], Syy);
-          }
-          // dL/dOmega_bar = 1/2 Omega^-1 S Omega^-1 (Oxy on both off-diagonal
-          // entries), in float64: its edge component is ~(k2/k1)^2 of its size.
-          const double ia = O[2] * idet, ib = -O[1] * idet, ic_ = O[0] * idet;
-          const double Sxx_d = Sxx, Sxy_d = Sxy, Syy_d = Syy;
-          const double K11 = fma(ia, Sxx_d, ib * Sxy_d), K12 = fma(ia, Sxy_d, ib * Syy_d);
-          const double K21 = fma(ib, Sxx_d, ic_ * Sxy_d), K22 = fma(ib, Sxy_d, ic_ * Syy_d);
-          const double Gxx = 0.5 * fma(K11, ia, K12 * ib);
-          const double Gxy = fma(K11, ib, K12 * ic_);
-          const double Gyy = 0.5 * fma(K21, ib, K22 * ic_);
-          // dL/dp: the offsets, and Omega sampled at p / 2 - 1/2
-          const float gpx = (float)(fma(ia, (double)tx, ib * (double)ty) +
-                                    0.5 * fma(Gxx, dOx[0], fma(Gxy, dOx[1], Gyy * dOx[2])));
-          const float gpy = (float)(fma(ib, (double)tx, ic_ * (double)ty) +
-                                    0.5 * fma(Gxx, dOy[0], fma(Gxy, dOy[1], Gyy * dOy[2])));
-          // dL/dk1, dL/dk2 at each corner: projections of dL/dOmega on its edge and
-          // gradient directions, 1/2 tr +- (cos 2phi U + sin 2phi V); then times dk/dtheta
-          const double T = 0.5 * (Gxx + Gyy), U = 0.5 * (Gyy - Gxx), V = -0.5 * Gxy;
-          const float ffx = (float)fx, ffy = (float)fy;
-          const float wq[4] = {(1.f - ffx) * (1.f - ffy), ffx * (1.f - ffy), (1.f - ffx) * ffy, ffx * ffy};
-          const int cq[4] = {ob, ob + 1, ob + ow, ob + ow + 1};
-          float s6[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const double2 dir = sm.sDir[cq[q]];
-            const float4 P0 = sm.sP[0][cq[q]], P1 = sm.sP[1][cq[q]];
-            const float2 P2 = sm.sP2[cq[q]];
-            const double qq = fma(dir.x, U, dir.y * V);
-            const float k1 = wq[q] * (float)(T + qq), k2 = wq[q] * (float)(T - qq);
-            s6[0] = fmaf(k1, P0.x, fmaf(k2, P0.y, s6[0]));
-            s6[1] = fmaf(k1, P0.z, fmaf(k2, P0.w, s6[1]));
-            s6[2] = fmaf(k1, P1.z, fmaf(k2, P1.w, s6[2]));
-            s6[3] = fmaf(k1, P2.x, fmaf(k2, P2.y, s6[3]));
-            s6[4] = fmaf(k1, P1.x, s6[4]);
-            s6[5] = fmaf(k2, P1.y, s6[5]);
-          }
-#pragma unroll
-          for (int e = 0; e < 6; ++e) acc[e] += (double)s6[e];
-          pgr[p] = grho;
-          pgx[p] = gpx;
-          pgy[p] = gpy;
-        }
-      }
-      if (whole || ++seg >= ntiles) break;
-      __syncthreads();
-    }
-
-    if (!is_ref) {
-      // over each of this wave's pixel rows, in registers: dL/dp summed per
-      // alignment tile column (both rows at once when they share a tile row)
-      // and dL/drho summed per R_hat corner column
-      const int r0 = wave * BPX;
-      const int runs = sm.sRun[lane];
-      const int run_t = runs & 127, run_a = (runs >> 8) & 127, run_b = (runs >> 16) & 127;
-      const bool end_t = (runs >> 7) & 1, end_a = (runs >> 15) & 1, end_b = (runs >> 23) & 1;
-      bool joined = false;
-      if (BPX == 2) joined = r0 + 1 >= nrow || sm.sTyRow[r0] == sm.sTyRow[r0 + 1];  // uniform
-#pragma unroll
-      for (int p = 0; p < BPX; ++p) {
-        const int r = r0 + p;
-        if (r >= nrow) continue;  // uniform
-        if (!(joined && p == 1)) {
-          double sx = (double)pgx[p], sy = (double)pgy[p];
-          if (joined && BPX == 2) {
-            sx += (double)pgx[1];
-            sy += (double)pgy[1];
-          }
-          sx = run_sum(sx, lane, run_t);
-          sy = run_sum(sy, lane, run_t);
-          if (end_t) {
-            sm.sHm[fi & 1][r][txl] = make_double2(sx, sy);
-            if (joined && BPX == 2 && r + 1 < nrow) sm.sHm[fi & 1][r + 1][txl] = make_double2(0.0, 0.0);
-          }
-        }
-        if (lane < rhw) {
-          sm.sHa[fi & 1][r][lane] = 0.f;
-          sm.sHb[fi & 1][r][lane] = 0.f;
-        }
-        const float ga = run_sum((1.f - rfx) * pgr[p], lane, run_a);
-        const float gb = run_sum(rfx * pgr[p], lane, run_b);
-        if (end_a) sm.sHa[fi & 1][r][rxa] = ga;
-        if (end_b) sm.sHb[fi & 1][r][rxb] = gb;
-      }
+    for (int i = 0; i < BRHT; ++i) {
+      const int k = min(tid + i * BTHREADS, nrh - 1);
+      const int r = split_row(k, inv);
+      rho_off[i] = ((rhr0 + r) * g.w + rhc0 + k - r * rhw) * 4;  // below 2^30
     }
   }
+  const int rpar = g.red_pos >> 1, gpar = (rpar ^ g.red_pos ^ 1) & 1;  // colour parities, as in the forward
+  unsigned typack = 0;  // alignment tile row of each of this wave's pixel rows, four bits each
+#pragma unroll
+  for (int p = 0; p < BPX; ++p) {
+    const int r = wave * BPX + p;
+    const int t = __builtin_amdgcn_readfirstlane(sm.sTyRow[r]) - tyA;
+    typack |= (unsigned)(r < nrow ? t : 0) << (4 * p);
+  }
+  const RowInfo* rowv = sm.sRow + (tid >> 6) * BPX;
+  const double* yv = sm.sY + (tid >> 6) * BPX;
+  const float* sRaw = (const float*)sm.sRaw;
+
+  auto bounds_of = [&](int slot) {
+    Bounds bd;
+    const int* b = sm.sBox[slot];
+    bd.jc0 = __builtin_amdgcn_readfirstlane(b[0]);
+    bd.jc1 = -__builtin_amdgcn_readfirstlane(b[1]);
+    bd.ic0 = __builtin_amdgcn_readfirstlane(b[2]);
+    bd.ic1 = -__builtin_amdgcn_readfirstlane(b[3]);
+    bd.hj0 = __builtin_amdgcn_readfirstlane(b[4]);
+    bd.hj1 = -__builtin_amdgcn_readfirstlane(b[5]);
+    bd.hi0 = __builtin_amdgcn_readfirstlane(b[6]);
+    bd.hi1 = -__builtin_amdgcn_readfirstlane(b[7]);
+    return bd;
+  };
+  auto fits = [&](const Win& w) { return w.ow * w.oh <= BCP::OM && w.lw * w.lh <= BCP::LUMA; };
+  // Every quad of a window in flight (two 32-bit loads each), as the forward
+  // stages them; the second per thread only where the window needs it.
+  uint32_t qt[BQB], qb[BQB];
+  float rhv[BRHT];
+  auto quad_load = [&](const Win& w, const uint16_t* f) {
+    const __amdgpu_buffer_rsrc_t rs = tile_rsrc(f, (size_t)g.H * g.W * 2);
+    const float inv = window_inv(w.lw);
+    const int nq = w.lw * w.lh, t = here(tid);
+#pragma unroll
+    for (int i = 0; i < BQB; ++i) {
+      if (i * BTHREADS >= nq) break;  // uniform
+      const int k = min(t + i * BTHREADS, nq - 1);
+      const int r = split_row(k, inv), c = k - mul24(r, w.lw);
+      const int I = min(max(w.lr0 + r, 0), g.h - 1), J = min(max(w.lc0 + c, 0), g.w - 1);
+      const int o = (int)((unsigned)I * (unsigned)(4 * g.W)) + 4 * J;  // bytes, below 2^31
+      qt[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, o, 0, 0);
+      qb[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, o, 2 * g.W, 0);
+    }
+  };
+  auto quad_store = [&](const Win& w) {
+    const float inv = window_inv(w.lw);
+    const int nq = w.lw * w.lh, t = here(tid);
+#pragma unroll
+    for (int i = 0; i < BQB; ++i) {
+      const int k = t + i * BTHREADS;
+      if (k >= nq) break;
+      const int r = split_row(k, inv), c = k - mul24(r, w.lw), at = 2 * k - c;
+      const bool in = (unsigned)(w.lr0 + r) < (unsigned)g.h && (unsigned)(w.lc0 + c) < (unsigned)g.w;
+      const float a0 = (float)(qt[i] & 0xffffu), a1 = (float)(qt[i] >> 16);
+      const float b0 = (float)(qb[i] & 0xffffu), b1 = (float)(qb[i] >> 16);
+      sm.sLum[k] = (a0 + a1) + (b0 + b1);  // exact
+      sm.sRaw[at] = in ? make_float2(a0, a1) : make_float2(0.f, 0.f);
+      sm.sRaw[at + w.lw] = in ? make_float2(b0, b1) : make_float2(0.f, 0.f);
+    }
+  };
+  auto prefetch = [&](int n, int slot) {
+    if (n != g.ref) {
+      const size_t plane = (size_t)g.h * g.w;
+      const __amdgpu_buffer_rsrc_t rs = tile_rsrc(rmin + (size_t)n * plane, plane * 4);
+#pragma unroll
+      for (int i = 0; i < BRHT; ++i) {
+        const uint32_t u = __builtin_amdgcn_raw_buffer_load_b32(rs, rho_off[i], 0, 0);
+        rhv[i] = __uint_as_float(u);
+      }
+    }
+    const Win w = make_win(bounds_of(slot), g);
+    if (fits(w)) quad_load(w, frames + (size_t)n * g.H * g.W);
+  };
+
+  const int per_chunk = min(FCH, BNV / ntiles);
+  for (int f0 = 0; f0 < g.n; f0 += per_chunk) {
+    const int nf = min(per_chunk, g.n - f0);
+    // displacements and footprints of the next nf frames (as the forward)
+    for (int k = here(tid); k < nf * 8; k += BTHREADS) (&sm.sBox[0][0])[k] = 0x7fffffff;
+    __syncthreads();
+    for (int k = here(tid); k < nf * ntiles; k += BTHREADS) {
+      const int slot = k / ntiles, t = k - slot * ntiles, ky = t / ntx, kx = t - ky * ntx;
+      const int n = frame_of(f0 + slot);
+      float2 v = make_float2(0.f, 0.f);
+      if (n != g.ref) {
+        const float* q = motion + (((size_t)n * g.TY + tyA + ky) * g.TX + txA + kx) * 2;
+        v = make_float2(q[0], q[1]);
+      }
+      // clamping keeps non-finite or huge vectors finite and changes no result
+      v = make_float2(fminf(fmaxf(v.x, -vlim), vlim), fminf(fmaxf(v.y, -vlim), vlim));
+      sm.sV[k] = v;
+      const Bounds b = footprint(sm.sX[sm.sClo[kx]] + (double)v.x, sm.sX[sm.sChi[kx]] + (double)v.x,
+                                 sm.sY[sm.sRlo[ky]] + (double)v.y, sm.sY[sm.sRhi[ky]] + (double)v.y, g);
+      int* red = sm.sBox[slot];
+      atomicMin(&red[0], b.jc0); atomicMin(&red[1], -b.jc1);
+      atomicMin(&red[2], b.ic0); atomicMin(&red[3], -b.ic1);
+      atomicMin(&red[4], b.hj0); atomicMin(&red[5], -b.hj1);
+      atomicMin(&red[6], b.hi0); atomicMin(&red[7], -b.hi1);
+    }
+    __syncthreads();
+    prefetch(frame_of(f0), 0);
+
+    for (int slot = 0; slot < nf; ++slot) {
+      const int fi = f0 + slot, n = frame_of(fi);
+      const bool is_ref = n == g.ref;
+      const uint16_t* f = frames + (size_t)n * g.H * g.W;
+      if (slot) __syncthreads();  // the previous frame's windows are no longer read, its row sums complete
+      if (!is_ref) {
+        const int t = here(tid);
+  #pragma unroll
+        for (int i = 0; i < BRHT; ++i)
+          if (t + i * BTHREADS < rhw * rhh) sm.sRh[t + i * BTHREADS] = rhv[i];
+      }
+      if (fi >= 2) add_rows(frame_of(fi - 1));  // frame 0 is the base frame: no sums
+      // this frame's dL/drho and dL/dp of the thread's pixels (0 where skipped)
+      float pgr[BPX], pgx[BPX], pgy[BPX];
+  #pragma unroll
+      for (int p = 0; p < BPX; ++p) pgr[p] = pgx[p] = pgy[p] = 0.f;
+
+      const Win whole_w = make_win(bounds_of(slot), g);
+      const bool whole = fits(whole_w);
+      const int nseg = whole ? 1 : ntiles;
+      for (int seg = 0; seg < nseg; ++seg) {
+        if (seg) __syncthreads();  // the previous alignment tile's windows are no longer read
+        const int sty = whole ? -1 : seg / ntx, stx = whole ? -1 : seg - sty * ntx;
+        // the forward's windows (one alignment tile's always fit: its footprint
+        // stops at the frame's ring)
+        Win wn = whole_w;
+        if (!whole) {
+          const float2 v = sm.sV[slot * ntiles + seg];
+          const Bounds b = footprint(sm.sX[sm.sClo[stx]] + (double)v.x, sm.sX[sm.sChi[stx]] + (double)v.x,
+                                     sm.sY[sm.sRlo[sty]] + (double)v.y, sm.sY[sm.sRhi[sty]] + (double)v.y, g);
+          Bounds u;
+          u.jc0 = __builtin_amdgcn_readfirstlane(b.jc0);
+          u.jc1 = __builtin_amdgcn_readfirstlane(b.jc1);
+          u.ic0 = __builtin_amdgcn_readfirstlane(b.ic0);
+          u.ic1 = __builtin_amdgcn_readfirstlane(b.ic1);
+          u.hj0 = __builtin_amdgcn_readfirstlane(b.hj0);
+          u.hj1 = __builtin_amdgcn_readfirstlane(b.hj1);
+          u.hi0 = __builtin_amdgcn_readfirstlane(b.hi0);
+          u.hi1 = __builtin_amdgcn_readfirstlane(b.hi1);
+          wn = make_win(u, g);
+          quad_load(wn, f);
+        }
+        quad_store(wn);
+        const int oc0 = wn.oc0, ow = wn.ow, or0 = wn.or0, oh = wn.oh;
+        const int lc0 = wn.lc0, lr0 = wn.lr0, lw = wn.lw;
+        const int rc0 = wn.rc0, rr0 = wn.rr0, rw = wn.rw;
+        __syncthreads();
+        {
+          const float inv = window_inv(ow);
+          for (int k = here(tid); k < ow * oh; k += BTHREADS) {
+            const int r = split_row(k, inv), c = k - mul24(r, ow);
+            const int I = min(max(or0 + r, 0), g.h - 1), J = min(max(oc0 + c, 0), g.w - 1);
+            const int base = mul24(I - 1 - lr0, lw) + (J - 1 - lc0);  // the window's ring repeats the edges
+            float l[3][3];
+  #pragma unroll
+            for (int a = 0; a < 3; ++a)
+  #pragma unroll
+              for (int bb = 0; bb < 3; ++bb) l[a][bb] = sm.sLum[base + a * lw + bb];
+            double oxx, oxy, oyy;
+            OmegaParts pt;
+            omega_parts_from_quads(l, mc.om, oxx, oxy, oyy, pt);
+            sm.sOm[0][k] = oxx;
+            sm.sOm[1][k] = oxy;
+            sm.sOm[2][k] = oyy;
+            // sigma_1,2 = k1s, k2s (k1 = sigma_1^2): per unit dL/dk1, dL/dk2 the
+            // derivatives of sigma_1,2 in every scalar, each times 2 sigma.
+            const double D = pt.D, A = pt.A, invA = pt.invA;
+            const double s1 = 2.0 * pt.k1s, s2 = 2.0 * pt.k2s;
+            const double f1 = pt.d_free ? s1 * (bc.kn - bc.kst * A) : 0.0;
+            const double f2 = pt.d_free ? s2 * (bc.kn - invA * bc.iksh) : 0.0;
+            const double sl = pt.sqrt_l1 * bc.sl;
+            sm.sDir[k] = make_double2(pt.c2, pt.s2);
+            sm.sP[0][k] = make_float4((float)(s1 * pt.k1s), (float)(s2 * pt.k2s), (float)(s1 * D), (float)(s2 * D));
+            sm.sP[1][k] = make_float4((float)(s1 * (1.0 - D) * A), (float)(s2 * (1.0 - D) * invA), (float)f1,
+                                      (float)f2);
+            sm.sP2[k] = make_float2((float)(f1 * sl), (float)(f2 * sl));
+          }
+        }
+        __syncthreads();
+
+        if (col_ok) {
+  #pragma unroll
+          for (int p = 0; p < BPX; ++p) {
+            const int r = wave * BPX + p;
+            if (r >= nrow) break;
+            const int tyl = (int)(typack >> (4 * p)) & 15;
+            if (!whole && (tyl != sty || txl != stx)) continue;
+            float rho = 1.f;
+            if (!is_ref) {
+              const RowInfo ri = rowv[p];
+              const float top = sm.sRh[ri.ya + rxa] + rfx * (sm.sRh[ri.ya + rxb] - sm.sRh[ri.ya + rxa]);
+              const float bot = sm.sRh[ri.yb + rxa] + rfx * (sm.sRh[ri.yb + rxb] - sm.sRh[ri.yb + rxa]);
+              rho = top + ri.fy * (bot - top);
+              if (!(rho > 0.f)) continue;
+            }
+            const float2 v = sm.sV[slot * ntiles + mul24(tyl, ntx) + txl];
+            const double px = X + (double)v.x, py = yv[p] + (double)v.y;
+            const double fjc = floor(px), fic = floor(py);
+            const double frx = px - fjc, fry = py - fic;
+            const int jc = (int)fjc, ic = (int)fic;
+            if (samples_outside(jc, ic, g)) continue;  // no in-frame sample: no term, no gradient
+            const double hx = px * 0.5 - 0.5, hy = py * 0.5 - 0.5;
+            const double fhj = floor(hx), fhi = floor(hy);
+            const double fx = hx - fhj, fy = hy - fhi;
+            const int ob = mul24((int)fhi - or0, ow) + ((int)fhj - oc0);
+            double O[3], dOx[3], dOy[3];  // Omega_bar and its derivatives along hx, hy
+  #pragma unroll
+            for (int e = 0; e < 3; ++e) {
+              const double o00 = sm.sOm[e][ob], o01 = sm.sOm[e][ob + 1];
+              const double o10 = sm.sOm[e][ob + ow], o11 = sm.sOm[e][ob + ow + 1];
+              const double top = fma(fx, o01 - o00, o00);
+              const double bot = fma(fx, o11 - o10, o10);
+              O[e] = fma(fy, bot - top, top);
+              dOx[e] = fma(fy, (o11 - o10) - (o01 - o00), o01 - o00);
+              dOy[e] = bot - top;
+            }
+            const double idet = recip64_1(O[0] * O[2] - O[1] * O[1]);
+            const double sc = NEG_HALF_LOG2E * idet;
+            const double qa = O[2] * sc, qb2 = -2.0 * O[1] * sc, qc = O[0] * sc;
+            double dx[3], dy[3];
+            float dxf[3], dyf[3];  // offsets of in-frame samples, 0 elsewhere
+  #pragma unroll
+            for (int j = 0; j < 3; ++j) {
+              dx[j] = ((double)j - 0.5) - frx;
+              dy[j] = ((double)j - 0.5) - fry;
+              const int qj = jc + j - 1, qi = ic + j - 1;
+              const bool okx = qj >= 0 && qj < g.W, oky = qi >= 0 && qi < g.H;
+              dxf[j] = okx ? (float)dx[j] : 0.f;
+              dyf[j] = oky ? (float)dy[j] : 0.f;
+              if (!okx) dx[j] = FAR_X;
+              if (!oky) dy[j] = FAR_Y;
+            }
+            // exponent of sample (i, j): (qa dx[j] + by[i]) dx[j] + cy[i], as the forward
+            double cy[3], by[3];
+  #pragma unroll
+            for (int i = 0; i < 3; ++i) {
+              by[i] = qb2 * dy[i];
+              cy[i] = qc * (dy[i] * dy[i]);
+            }
+            // channel of each colour group: centre (0), left/right (1), up/down (2), corners (3)
+            const bool isG = ((ic ^ jc ^ gpar) & 1) == 0;
+            const bool xIsR = ((ic ^ rpar) & 1) == 0;  // group "X" (centre or left/right) is red
+            float Mg[4], Gg[4], Ch[4], Cl[4];
+            route4(mref[p], isG, xIsR, Mg);
+            route4(gam[p], isG, xIsR, Gg);
+            route4(chi[p], isG, xIsR, Ch);
+            route4(clo[p], isG, xIsR, Cl);
+            // the group's reference joins the row term
+            const double row[3][2] = {{cy[0] - (double)Mg[2], cy[0] - (double)Mg[3]},
+                                      {cy[1] - (double)Mg[0], cy[1] - (double)Mg[1]},
+                                      {cy[2] - (double)Mg[2], cy[2] - (double)Mg[3]}};
+            const int vb = mul24(ic - 1 - rr0, rw) + (jc - 1 - rc0);
+            float a[3][3];
+            float grho = 0.f;
+  #pragma unroll
+            for (int i = 0; i < 3; ++i)
+  #pragma unroll
+              for (int j = 0; j < 3; ++j) {
+                const int q = (i == 1 && j == 1) ? 0 : (i == 1 ? 1 : (j == 1 ? 2 : 3));
+                const float w = __builtin_amdgcn_exp2f(
+                    (float)fma(fma(qa, dx[j], by[i]), dx[j], row[i][j == 1 ? 0 : 1]));
+                const float bq = Gg[q] * w * ((sRaw[vb + i * rw + j] - Ch[q]) - Cl[q]);  // dL/drho part
+                grho += bq;
+                a[i][j] = rho * bq;  // dL/de
+              }
+            // S = sum a d d^T, t = sum a d (offsets separate into columns and rows)
+            float Acol[3], Arow[3], Sxy = 0.f;
+  #pragma unroll
+            for (int j = 0; j < 3; ++j) Acol[j] = a[0][j] + a[1][j] + a[2][j];
+  #pragma unroll
+            for (int i = 0; i < 3; ++i) {
+              Arow[i] = a[i][0] + a[i][1] + a[i][2];
+              Sxy = fmaf(dyf[i], fmaf(a[i][0], dxf[0], fmaf(a[i][1], dxf[1], a[i][2] * dxf[2])), Sxy);
+            }
+            float Sxx = 0.f, Syy = 0.f, tx = 0.f, ty = 0.f;
+  #pragma unroll
+            for (int j = 0; j < 3; ++j) {
+              tx = fmaf(Acol[j], dxf[j], tx);
+              Sxx = fmaf(Acol[j] * dxf[j], dxf[j], Sxx);
+              ty = fmaf(Arow[j], dyf[j], ty);
+              Syy = fmaf(Arow[j] * dyf[j], dyf[j], Syy);
+            }
+            // dL/dOmega_bar = 1/2 Omega^-1 S Omega^-1 (Oxy on both off-diagonal
+            // entries), in float64: its edge component is ~(k2/k1)^2 of its size.
+            const double ia = O[2] * idet, ib = -O[1] * idet, ic_ = O[0] * idet;
+            const double Sxx_d = Sxx, Sxy_d = Sxy, Syy_d = Syy;
+            const double K11 = fma(ia, Sxx_d, ib * Sxy_d), K12 = fma(ia, Sxy_d, ib * Syy_d);
+            const double K21 = fma(ib, Sxx_d, ic_ * Sxy_d), K22 = fma(ib, Sxy_d, ic_ * Syy_d);
+            const double Gxx = 0.5 * fma(K11, ia, K12 * ib);
+            const double Gxy = fma(K11, ib, K12 * ic_);
+            const double Gyy = 0.5 * fma(K21, ib, K22 * ic_);
+            // dL/dp: the offsets, and Omega sampled at p / 2 - 1/2
+            const float gpx = (float)(fma(ia, (double)tx, ib * (double)ty) +
+                                      0.5 * fma(Gxx, dOx[0], fma(Gxy, dOx[1], Gyy * dOx[2])));
+            const float gpy = (float)(fma(ib, (double)tx, ic_ * (double)ty) +
+                                      0.5 * fma(Gxx, dOy[0], fma(Gxy, dOy[1], Gyy * dOy[2])));
+            // dL/dk1, dL/dk2 at each corner: projections of dL/dOmega on its edge and
+            // gradient directions, 1/2 tr +- (cos 2phi U + sin 2phi V); then times dk/dtheta
+            const double T = 0.5 * (Gxx + Gyy), U = 0.5 * (Gyy - Gxx), V = -0.5 * Gxy;
+            const float ffx = (float)fx, ffy = (float)fy;
+            const float wq[4] = {(1.f - ffx) * (1.f - ffy), ffx * (1.f - ffy), (1.f - ffx) * ffy, ffx * ffy};
+            const int cq[4] = {ob, ob + 1, ob + ow, ob + ow + 1};
+            float s6[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  #pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const double2 dir = sm.sDir[cq[q]];
+              const float4 P0 = sm.sP[0][cq[q]], P1 = sm.sP[1][cq[q]];
+              const float2 P2 = sm.sP2[cq[q]];
+              const double qq = fma(dir.x, U, dir.y * V);
+              const float k1 = wq[q] * (float)(T + qq), k2 = wq[q] * (float)(T - qq);
+              s6[0] = fmaf(k1, P0.x, fmaf(k2, P0.y, s6[0]));
+              s6[1] = fmaf(k1, P0.z, fmaf(k2, P0.w, s6[1]));
+              s6[2] = fmaf(k1, P1.z, fmaf(k2, P1.w, s6[2]));
+              s6[3] = fmaf(k1, P2.x, fmaf(k2, P2.y, s6[3]));
+              s6[4] = fmaf(k1, P1.x, s6[4]);
+              s6[5] = fmaf(k2, P1.y, s6[5]);
+            }
+  #pragma unroll
+            for (int e = 0; e < 6; ++e) acc[e] += (double)s6[e];
+            pgr[p] = grho;
+            pgx[p] = gpx;
+            pgy[p] = gpy;
+          }
+        }
+      }
+      // the next frame's first loads, under this frame's row sums
+      if (slot + 1 < nf) prefetch(frame_of(fi + 1), slot + 1);
+
+      if (!is_ref) {
+        // over each of this wave's pixel rows, in registers: dL/dp summed per
+        // alignment tile column (both rows at once when they share a tile row)
+        // and dL/drho summed per R_hat corner column
+        const int r0 = wave * BPX;
+        const int runs = sm.sRun[lane];
+        const int run_t = runs & 127, run_a = (runs >> 8) & 127, run_b = (runs >> 16) & 127;
+        const bool end_t = (runs >> 7) & 1, end_a = (runs >> 15) & 1, end_b = (runs >> 23) & 1;
+        bool joined = false;
+        if (BPX == 2) joined = r0 + 1 >= nrow || sm.sTyRow[r0] == sm.sTyRow[r0 + 1];  // uniform
+  #pragma unroll
+        for (int p = 0; p < BPX; ++p) {
+          const int r = r0 + p;
+          if (r >= nrow) continue;  // uniform
+          if (!(joined && p == 1)) {
+            double sx = (double)pgx[p], sy = (double)pgy[p];
+            if (joined && BPX == 2) {
+              sx += (double)pgx[1];
+              sy += (double)pgy[1];
+            }
+            sx = run_sum(sx, lane, run_t);
+            sy = run_sum(sy, lane, run_t);
+            if (end_t) {
+              sm.sHm[r][txl] = make_double2(sx, sy);
+              if (joined && BPX == 2 && r + 1 < nrow) sm.sHm[r + 1][txl] = make_double2(0.0, 0.0);
+            }
+          }
+          if (lane < rhw) {
+            sm.sHa[r][lane] = 0.f;
+            sm.sHb[r][lane] = 0.f;
+          }
+          const float ga = run_sum((1.f - rfx) * pgr[p], lane, run_a);
+          const float gb = run_sum(rfx * pgr[p], lane, run_b);
+          if (end_a) sm.sHa[r][rxa] = ga;
+          if (end_b) sm.sHb[r][rxb] = gb;
+        }
+      }
+    }
+    // the displacements are no longer read, the last frame's row sums complete
+    __syncthreads();
+  }
   // the last frame's row sums (a burst of the base frame alone has none)
-  __syncthreads();
-  if (g.n >= 2) add_rows((g.n - 1) & 1, frame_of(g.n - 1));
+  if (g.n >= 2) add_rows(frame_of(g.n - 1));
 
   // ---- the six covariance-scalar sums of the workgroup ------------------
 #pragma unroll

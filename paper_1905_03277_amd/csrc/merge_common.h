@@ -21,6 +21,23 @@ constexpr double FAR_X = 1e100, FAR_Y = 1e120;
 // terms land in [1e11, 1e38] and the cross term stays below 1e31.
 constexpr float FAR_X32 = 1e8f, FAR_Y32 = 1e16f;
 
+// The same value, as if computed here: index arithmetic on it stays inside the
+// frame loop instead of being hoisted out of it, where some forty values held
+// across the pixel arithmetic spilled it at the 128-VGPR budget of k_merge.
+__device__ __forceinline__ int here(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// Raw buffer resource over `bytes` bytes (at most 2^31) from p, a uniform
+// pointer (word 3 as for gfx9 raw buffers).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const void* p, size_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)bytes, 0x00020000);
+}
+
+// Frames whose displacements and footprints are staged at once, at most.
+constexpr int FCH = 16;
+
 template <int MH>
 struct Caps {
   // sized for scale 1 with up to ~8 px of displacement spread inside the tile

@@ -57,7 +57,6 @@ namespace hmfsr {
 namespace {
 
 constexpr float SLACK = 64.f;   // log2 headroom above the reference exponent
-constexpr int FCH = 16;         // frames whose displacements and footprints are staged at once, at most
 
 template <int MH>
 struct MergeSmem {
@@ -95,20 +94,6 @@ struct StreamState {
   float* out;
   int first;
 };
-
-// The same value, as if computed here: index arithmetic on it stays inside the
-// frame loop instead of being hoisted out of it, where some forty values held
-// across the pixel arithmetic spilled it at the 128-VGPR budget.
-__device__ __forceinline__ int here(int v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-
-// Raw buffer resource over `bytes` bytes (at most 2^31) from p, a uniform
-// pointer (word 3 as for gfx9 raw buffers).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const void* p, size_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)bytes, 0x00020000);
-}
 
 // One 64 x MH output tile (tile_x, tile_y) of one burst. RB: raw-footprint
 // samples a thread loads at once (quads of four; see wide_raw_window).
