@@ -255,6 +255,26 @@ hmfsr_status make_align_geom(const hmfsr_desc* d, const hmfsr_align_params* p, A
 }
 }  // namespace
 
+namespace {
+// The motion prior, the guide statistics and the robustness. Between
+// hmfsr_profile_begin and hmfsr_profile_end the prior is a launch of its own,
+// so that its stage can be timed; else it shares the statistics' launch.
+hipError_t run_robust(const Geometry& g, const RobustConsts& rc, const PriorConsts& pc, const uint16_t* frames,
+                      const float* motion, const Work& w, float* rmin, float* robust, hipStream_t s, bool profiled) {
+  hipError_t err;
+  if (profiled && g_timing.on) {
+    if ((err = timed(HMFSR_STAGE_PRIOR, s, [&] { return launch_prior(g, pc, motion, w, s); })) != hipSuccess)
+      return err;
+    return timed(HMFSR_STAGE_ROBUST, s, [&] {
+      const hipError_t e = launch_guide_stats(g, rc, frames, w, s);
+      return e != hipSuccess ? e : launch_robust(g, rc, motion, w, rmin, robust, s);
+    });
+  }
+  if ((err = launch_guide(g, rc, pc, frames, motion, w, s)) != hipSuccess) return err;
+  return launch_robust(g, rc, motion, w, rmin, robust, s);
+}
+}  // namespace
+
 hmfsr_status run_merge(const hmfsr_desc* desc, const hmfsr_tuning* tuning, const Geometry& g,
                        const uint16_t* frames, const float* motion, float* out, float* saved,
                        const Work& w, int variant, hipStream_t s, bool profiled) {
@@ -262,11 +282,7 @@ hmfsr_status run_merge(const hmfsr_desc* desc, const hmfsr_tuning* tuning, const
   const RobustConsts rc = make_robust(desc, tuning);
   const MergeConsts mc = make_merge(desc, tuning, g);
   auto run = [&](int stage, auto fn) { return profiled ? timed(stage, s, fn) : fn(); };
-  if (run(HMFSR_STAGE_PRIOR, [&] { return launch_prior(g, pc, motion, w, s); }) != hipSuccess)
-    return HMFSR_E_HIP;
-  if (run(HMFSR_STAGE_ROBUST, [&] { return launch_robust(g, rc, frames, motion, w, w.rmin, nullptr, s); }) !=
-      hipSuccess)
-    return HMFSR_E_HIP;
+  if (run_robust(g, rc, pc, frames, motion, w, w.rmin, nullptr, s, profiled) != hipSuccess) return HMFSR_E_HIP;
   if (run(HMFSR_STAGE_MERGE, [&] { return launch_merge(variant, g, mc, frames, motion, w.rmin, out, saved, s); }) !=
       hipSuccess)
     return HMFSR_E_HIP;
@@ -349,10 +365,7 @@ hmfsr_status hmfsr_stream_add(const hmfsr_desc* desc, const hmfsr_tuning* tuning
   const PriorConsts pc = make_prior(tuning);
   const RobustConsts rc = make_robust(desc, tuning);
   const MergeConsts mc = make_merge(desc, tuning, g);
-  if (timed(HMFSR_STAGE_PRIOR, s, [&] { return launch_prior(g, pc, mo, w, s); }) != hipSuccess ||
-      timed(HMFSR_STAGE_ROBUST, s, [&] {
-        return launch_robust(g, rc, frames, mo, w, w.rmin, nullptr, s);
-      }) != hipSuccess ||
+  if (run_robust(g, rc, pc, frames, mo, w, w.rmin, nullptr, s, true) != hipSuccess ||
       timed(HMFSR_STAGE_MERGE, s, [&] {
         return launch_merge_stream(g, mc, frames, mo, w.rmin, state, state, 1, s);
       }) != hipSuccess)
@@ -408,12 +421,7 @@ hmfsr_status hmfsr_merge_backward(const hmfsr_desc* desc, const hmfsr_tuning* tu
   bc.tiles_x = (g.OW + 63) / 64;
   bc.tiles_y = (g.OH + kBwdRows - 1) / kBwdRows;
   bc.n_tiles = bc.tiles_x * bc.tiles_y;
-  if (timed(HMFSR_STAGE_PRIOR, s, [&] { return launch_prior(g, pc, motion, w.fwd, s); }) != hipSuccess)
-    return HMFSR_E_HIP;
-  if (timed(HMFSR_STAGE_ROBUST, s, [&] {
-        return launch_robust(g, rc, frames, motion, w.fwd, w.fwd.rmin, w.rmap, s);
-      }) != hipSuccess)
-    return HMFSR_E_HIP;
+  if (run_robust(g, rc, pc, frames, motion, w.fwd, w.fwd.rmin, w.rmap, s, true) != hipSuccess) return HMFSR_E_HIP;
   if (need_saved) {
     if (timed(HMFSR_STAGE_MERGE, s, [&] {
           return launch_merge(merge_variant(g), g, mc, frames, motion, w.fwd.rmin, nullptr, w.saved, s);
@@ -457,8 +465,9 @@ hmfsr_status hmfsr_merge_maps(const hmfsr_desc* desc, const hmfsr_tuning* tuning
     return HMFSR_E_HIP;
   if (launch_prior(g, make_prior(tuning), motion, w, s) != hipSuccess) return HMFSR_E_HIP;
   float* rmin = robust_min ? robust_min : w.rmin;
-  if (launch_robust(g, make_robust(desc, tuning), frames, motion, w, rmin, robust, s) !=
-      hipSuccess)
+  const RobustConsts rc = make_robust(desc, tuning);
+  if (launch_guide_stats(g, rc, frames, w, s) != hipSuccess ||
+      launch_robust(g, rc, motion, w, rmin, robust, s) != hipSuccess)
     return HMFSR_E_HIP;
   // the base frame's robustness is 1 by definition
   for (float* m : {robust, robust_min}) {

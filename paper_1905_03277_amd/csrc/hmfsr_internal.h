@@ -89,11 +89,16 @@ Work work_carve(void* base, const Geometry& g);
 // Rejection strength into w.s_tile and the prior's choice into w.mov.
 hipError_t launch_prior(const Geometry& g, const PriorConsts& pc, const float* motion, const Work& w,
                         hipStream_t stream);
-// Guide statistics into w.gmu / w.gref, then R_hat into rmin (and R into
-// robust, nullable); reads w.s_tile.
-hipError_t launch_robust(const Geometry& g, const RobustConsts& rc, const uint16_t* frames,
-                         const float* motion, const Work& w, float* rmin, float* robust,
-                         hipStream_t stream);
+// Guide statistics into w.gmu / w.gref.
+hipError_t launch_guide_stats(const Geometry& g, const RobustConsts& rc, const uint16_t* frames, const Work& w,
+                              hipStream_t stream);
+// launch_prior and launch_guide_stats in one launch (nothing for a burst of
+// the base frame alone, whose prior and statistics nothing reads).
+hipError_t launch_guide(const Geometry& g, const RobustConsts& rc, const PriorConsts& pc, const uint16_t* frames,
+                        const float* motion, const Work& w, hipStream_t stream);
+// R_hat into rmin (and R into robust, nullable) from the prior and the statistics.
+hipError_t launch_robust(const Geometry& g, const RobustConsts& rc, const float* motion, const Work& w, float* rmin,
+                         float* robust, hipStream_t stream);
 // Compiled tile shapes of the merge kernel (64 columns x rows, threads).
 struct MergeVariant {
   const char* name;

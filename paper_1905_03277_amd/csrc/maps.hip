@@ -9,21 +9,6 @@ namespace {
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-// eq. (7)-(8): rejection strength s1 or s2 per tile.
-__device__ __forceinline__ void prior_one(const float* __restrict__ motion, const Geometry& g,
-                                          const PriorConsts& pc, float* __restrict__ s_tile,
-                                          unsigned char* __restrict__ mov, int n, int ty, int tx) {
-  const size_t idx = ((size_t)n * g.TY + ty) * g.TX + tx;
-  if (n == g.ref) {
-    s_tile[idx] = 0.0f;
-    mov[idx] = 0;
-    return;
-  }
-  const bool moving = prior_moving(motion, g, pc.m_th, n, ty, tx);
-  s_tile[idx] = moving ? pc.s1 : pc.s2;
-  mov[idx] = moving;
-}
-
 __global__ void k_prior(const float* __restrict__ motion, Geometry g, PriorConsts pc,
                         float* __restrict__ s_tile, unsigned char* __restrict__ mov) {
   const int tx = blockIdx.x * blockDim.x + threadIdx.x;

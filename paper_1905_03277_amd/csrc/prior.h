@@ -37,4 +37,19 @@ __device__ __forceinline__ bool prior_moving(const float* __restrict__ motion, c
   return m2 > __dmul_rn(m_th, m_th);
 }
 
+// eq. (7)-(8): rejection strength s1 or s2 per tile.
+__device__ __forceinline__ void prior_one(const float* __restrict__ motion, const Geometry& g,
+                                          const PriorConsts& pc, float* __restrict__ s_tile,
+                                          unsigned char* __restrict__ mov, int n, int ty, int tx) {
+  const size_t idx = ((size_t)n * g.TY + ty) * g.TX + tx;
+  if (n == g.ref) {
+    s_tile[idx] = 0.0f;
+    mov[idx] = 0;
+    return;
+  }
+  const bool moving = prior_moving(motion, g, pc.m_th, n, ty, tx);
+  s_tile[idx] = moving ? pc.s1 : pc.s2;
+  mov[idx] = moving;
+}
+
 }  // namespace hmfsr

@@ -30,10 +30,13 @@
 // 3x3 window of S (all integers below 2^53, so float64 holds them exactly);
 // where A < hf * 81 B (variance lost to the low-pass) and the tile's motion
 // prior chose s1 (eq. 8), R of the aligned frame is 0.
+#include <stddef.h>
+
 #include "device_util.h"
 #include "guide_maps.h"
 #include "hmfsr_internal.h"
 #include "noise.h"
+#include "prior.h"
 
 namespace hmfsr {
 namespace {
@@ -196,7 +199,7 @@ __global__ __launch_bounds__(THREADS) void k_frame_means_batch(const BurstArgs* 
 // ---- pass 1b: the base frame's statistics ------------------------------------------
 struct BaseSmem {
   float G[3][GW_N];  // guide at rows I0-2 .. I0+GM_H+1, columns J0-2 .., clamped to the grid
-  float S[3][GW_N];  // doubled 3x3 box sums (S.3)
+  float S[3][GW_N];  // doubled 3x3 box sums (S.3); neither touched nor allocated where rc.hf = 0
 };
 
 // One 64x16 tile (tile_x, tile_y): the base frame's 3x3 guide means into
@@ -317,12 +320,54 @@ __device__ __forceinline__ void base_stats_tile(const uint16_t* __restrict__ fra
   }
 }
 
+size_t base_smem_bytes(const RobustConsts& rc) { return rc.hf > 0.0 ? sizeof(BaseSmem) : offsetof(BaseSmem, S); }
+
 __global__ __launch_bounds__(THREADS) void k_base_stats(const uint16_t* __restrict__ frames, Geometry g,
                                                         RobustConsts rc, uint2* __restrict__ gmu,
                                                         float* __restrict__ gref) {
-  __shared__ BaseSmem sm;
+  extern __shared__ float dyn[];
+  BaseSmem& sm = *(BaseSmem*)dyn;
   const int tx_n = means_tiles_x(g), t = xcd_tile(blockIdx.x, tx_n * means_tiles_y(g));
   base_stats_tile(frames, g, rc, gmu, gref, t % tx_n, t / tx_n, sm);
+}
+
+// Everything a merge computes before the robustness, in one launch: the
+// aligned frames' sums (workgroups [0, n_means)), the base frame's statistics
+// (from n_means8, the count rounded up so that workgroup ids keep their XCD)
+// and the motion prior of every tile.
+//
+// The three do not depend on each other, and for small bursts each was a
+// launch of 4.5-5 us for 1-3 us of work. Without S.3 the base tiles take 16 KB
+// of LDS (the 32 KB they took before also without it would hold the streaming
+// part to four workgroups per unit), so one launch is the faster form at every
+// size: the 8 x 256 x 256 merge 68.9 -> 59.9 us, 5 x 750 x 1002 at scale 1.5
+// 118 -> 110 us, 12 MP x 8 989 -> 976 us, 3 MP x 8 streamed 673 -> 612 us.
+__global__ __launch_bounds__(THREADS) void k_guide(const uint16_t* __restrict__ frames,
+                                                   const float* __restrict__ motion, Geometry g, RobustConsts rc,
+                                                   PriorConsts pc, uint2* __restrict__ gmu, float* __restrict__ gref,
+                                                   float* __restrict__ s_tile, unsigned char* __restrict__ mov,
+                                                   int n_means, int n_base) {
+  extern __shared__ float dyn[];
+  const int n_means8 = (n_means + XCDS - 1) / XCDS * XCDS, n_base8 = (n_base + XCDS - 1) / XCDS * XCDS;
+  int b = blockIdx.x;
+  if (b < n_means8) {
+    if (b >= n_means) return;
+    const int i = xcd_tile(b, n_means), ns = fm_strips(g), per = ns * fm_bands(g);
+    const int m = i / per, t = i - m * per;
+    frame_means_block(frames, g, gmu, m < g.ref ? m : m + 1, t % ns, (t / ns) * FM_WAVES + (threadIdx.x >> 6));
+    return;
+  }
+  b -= n_means8;
+  if (b < n_base8) {
+    if (b >= n_base) return;
+    const int tx_n = means_tiles_x(g), t = xcd_tile(b, n_base);
+    base_stats_tile(frames, g, rc, gmu, gref, t % tx_n, t / tx_n, *(BaseSmem*)dyn);
+    return;
+  }
+  const int i = (b - n_base8) * THREADS + threadIdx.x, per = g.TY * g.TX;
+  if (i >= g.n * per) return;
+  const int n = i / per, t = i - n * per;
+  prior_one(motion, g, pc, s_tile, mov, n, t / g.TX, t % g.TX);
 }
 
 // Every (burst, tile) of a batch, one workgroup each, in XCD-contiguous runs.
@@ -617,17 +662,33 @@ int robust_tiles_y(const Geometry& g) { return robust_tiles_y_(g); }
 int base_stats_groups(const Geometry& g) { return g.n > 1 ? means_tiles_x(g) * means_tiles_y(g) : 0; }
 int frame_means_groups(const Geometry& g) { return g.n > 1 ? (g.n - 1) * fm_strips(g) * fm_bands(g) : 0; }
 
-hipError_t launch_robust(const Geometry& g, const RobustConsts& rc, const uint16_t* frames,
-                         const float* motion, const Work& w, float* rmin, float* robust,
-                         hipStream_t stream) {
+hipError_t launch_guide(const Geometry& g, const RobustConsts& rc, const PriorConsts& pc, const uint16_t* frames,
+                        const float* motion, const Work& w, hipStream_t stream) {
   if (g.n < 2) return hipSuccess;
-  hipLaunchKernelGGL(k_base_stats, dim3(means_tiles_x(g) * means_tiles_y(g)), dim3(THREADS), 0, stream, frames, g,
-                     rc, w.gmu, w.gref);
+  const int n_means = frame_means_groups(g), n_base = base_stats_groups(g);
+  auto up8 = [](int v) { return (v + XCDS - 1) / XCDS * XCDS; };
+  const long long tiles = (long long)g.n * g.TY * g.TX;
+  const unsigned groups = (unsigned)(up8(n_means) + up8(n_base)) + (unsigned)((tiles + THREADS - 1) / THREADS);
+  hipLaunchKernelGGL(k_guide, dim3(groups), dim3(THREADS), base_smem_bytes(rc), stream, frames, motion, g, rc, pc,
+                     w.gmu, w.gref, w.s_tile, w.mov, n_means, n_base);
+  return hipGetLastError();
+}
+
+hipError_t launch_guide_stats(const Geometry& g, const RobustConsts& rc, const uint16_t* frames, const Work& w,
+                              hipStream_t stream) {
+  if (g.n < 2) return hipSuccess;
+  hipLaunchKernelGGL(k_base_stats, dim3(means_tiles_x(g) * means_tiles_y(g)), dim3(THREADS), base_smem_bytes(rc),
+                     stream, frames, g, rc, w.gmu, w.gref);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   hipLaunchKernelGGL(k_frame_means, dim3(fm_strips(g) * fm_bands(g), g.n - 1), dim3(THREADS), 0, stream, frames,
                      g, w.gmu);
-  if ((err = hipGetLastError()) != hipSuccess) return err;
+  return hipGetLastError();
+}
+
+hipError_t launch_robust(const Geometry& g, const RobustConsts& rc, const float* motion, const Work& w, float* rmin,
+                         float* robust, hipStream_t stream) {
+  if (g.n < 2) return hipSuccess;
   // Frames per workgroup: all of them (the base statistics are loaded once
   // per tile) unless that leaves fewer than ~kRobustGroups workgroups, about
   // four rounds of the resident workgroups of a 256-CU device; then as few
