@@ -251,8 +251,10 @@ hmfsr_status hmfsr_merge_backward(const hmfsr_desc* desc, const hmfsr_tuning* tu
  *                       `motion` DEVICE float32 [TY][TX][2] (its tile
  *                       displacements), `base_frame` the same base frame as
  *                       for begin (its statistics drive the robustness, eq.
- *                       5-9). The frames are copied into a library workspace
- *                       of two frames; calls on one device must share a stream.
+ *                       5-9). Both frames and the vectors are read where they
+ *                       are, in stream order; the library workspace holds the
+ *                       maps of two frames. Calls on one device must share a
+ *                       stream.
  * hmfsr_stream_end   -- normalise `state` into `out` (eq. 1), as hmfsr_merge.
  */
 hmfsr_status hmfsr_stream_begin(const hmfsr_desc* desc, const hmfsr_tuning* tuning,

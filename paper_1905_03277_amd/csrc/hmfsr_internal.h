@@ -19,6 +19,7 @@ struct Geometry {
   int colour[4];    // colour (0 R, 1 G, 2 B) of Bayer parity (r & 1) * 2 + (c & 1)
   int green_pos[2]; // the two green parity indices, ascending
   int red_pos, blue_pos;
+  long long fstride;  // samples from a frame to the next (H W, or between two buffers of a streamed pair)
   double scale;
 };
 

@@ -32,7 +32,7 @@ struct DeviceState {
   size_t batch_ws_bytes = 0;
   void* bwd_ws = nullptr;     // adjoint workspace
   size_t bwd_ws_bytes = 0;
-  void* stream_ws = nullptr;  // streaming merge: two-frame view and its maps
+  void* stream_ws = nullptr;  // streaming merge: the maps of the base and the added frame
   size_t stream_ws_bytes = 0;
   void* align_ws = nullptr;   // tile alignment: pyramids and block vectors
   size_t align_ws_bytes = 0;

@@ -41,7 +41,7 @@ __global__ void k_omega_map(const uint16_t* __restrict__ frames, Geometry g, Ome
   const int I = blockIdx.y * blockDim.y + threadIdx.y;
   const int n = blockIdx.z;
   if (I >= g.h || J >= g.w) return;
-  const uint16_t* f = frames + (size_t)n * g.H * g.W;
+  const uint16_t* f = frames + n * g.fstride;
   int l[3][3];
   for (int a = 0; a < 3; ++a)
     for (int b = 0; b < 3; ++b) {

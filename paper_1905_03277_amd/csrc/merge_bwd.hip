@@ -416,7 +416,7 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
       }
     }
     const Win w = make_win(bounds_of(slot), g);
-    if (fits(w)) quad_load(w, frames + (size_t)n * g.H * g.W);
+    if (fits(w)) quad_load(w, frames + n * g.fstride);
   };
 
   const int per_chunk = min(FCH, BNV / ntiles);
@@ -450,7 +450,7 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
     for (int slot = 0; slot < nf; ++slot) {
       const int fi = f0 + slot, n = frame_of(fi);
       const bool is_ref = n == g.ref;
-      const uint16_t* f = frames + (size_t)n * g.H * g.W;
+      const uint16_t* f = frames + n * g.fstride;
       if (slot) __syncthreads();  // the previous frame's windows are no longer read, its row sums complete
       if (!is_ref) {
         const int t = here(tid);

@@ -559,13 +559,13 @@ __device__ __forceinline__ void merge_tile(const uint16_t* __restrict__ frames,
       const int n = frame_of(f0 + slot);
       const Frame nx = head(slot);
       if (n != g.ref) rh_load(n, q.rh);
-      if (nx.whole) quad_load(nx.w, frames + (size_t)n * g.H * g.W, here(tid), q.top, q.bot);
+      if (nx.whole) quad_load(nx.w, frames + n * g.fstride, here(tid), q.top, q.bot);
     };
     prefetch(0);
     for (int slot = 0; slot < nf; ++slot) {
       const int n = frame_of(f0 + slot);
       const bool is_ref = n == g.ref;
-      const uint16_t* f = frames + (size_t)n * g.H * g.W;
+      const uint16_t* f = frames + n * g.fstride;
       const Frame F = head(slot);
       if (slot) __syncthreads();  // the previous frame's windows are no longer read
       if (!is_ref) rh_store(q.rh);

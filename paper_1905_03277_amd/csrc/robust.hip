@@ -123,7 +123,7 @@ __device__ __forceinline__ void frame_means_block(const uint16_t* __restrict__ f
   const int J = strip * FM_COLS + lane, Jc = min(J, g.w - 1);
   const bool edge = lane == 0 || lane == 63;
   const int Jh = clampi(lane == 0 ? J - 1 : J + 1, 0, g.w - 1);  // the edge lanes' outer neighbour
-  const uint16_t* f = frames + (size_t)n * g.H * g.W;
+  const uint16_t* f = frames + n * g.fstride;
   const int ws = mu_stride(g);
   uint2* mu = gmu + (size_t)n * g.h * ws;
   // every row's quads first, so that the loads are all in flight together
@@ -210,7 +210,7 @@ __device__ __forceinline__ void base_stats_tile(const uint16_t* __restrict__ fra
   const int tid = threadIdx.x;
   const int I0 = tile_y * GM_H, J0 = tile_x * GM_W;
   const int gy0 = I0 - 2, gx0 = J0 - 2;
-  const uint16_t* f = frames + (size_t)g.ref * g.H * g.W;
+  const uint16_t* f = frames + g.ref * g.fstride;
   {
     // every quad of the window loaded before the first store
     constexpr int GPT = (GW_N + THREADS - 1) / THREADS;
