@@ -18,27 +18,27 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<MH, THREADS>())) void k_me
 }
 
 // Forward that also keeps the normaliser for the adjoint (float64 accumulation).
-template <int RB>
+template <int MH, int RB>
 __global__ __launch_bounds__(256, 2) void k_merge_save(
     const uint16_t* __restrict__ frames, const float* __restrict__ motion,
     const float* __restrict__ rmin, Geometry g, MergeConsts mc, float* __restrict__ out,
     float* __restrict__ saved) {
-  __shared__ MergeSmem<16> sm;
-  const int tiles_x = (g.OW + MW - 1) / MW, n = tiles_x * ((g.OH + 15) / 16);
+  __shared__ MergeSmem<MH> sm;
+  const int tiles_x = (g.OW + MW - 1) / MW, n = tiles_x * ((g.OH + MH - 1) / MH);
   const int t = xcd_tile(blockIdx.x, n);
-  merge_tile<16, 256, TILE_SAVE, RB>(frames, motion, rmin, g, mc, out, saved, StreamState{nullptr, nullptr, 0},
+  merge_tile<MH, 256, TILE_SAVE, RB>(frames, motion, rmin, g, mc, out, saved, StreamState{nullptr, nullptr, 0},
                                  t % tiles_x, t / tiles_x, sm);
 }
 
 // Streaming form: frames from loop index st.first on are added to the state.
-template <int RB>
+template <int MH, int RB>
 __global__ __launch_bounds__(256, 4) void k_merge_stream(
     const uint16_t* __restrict__ frames, const float* __restrict__ motion,
     const float* __restrict__ rmin, Geometry g, MergeConsts mc, StreamState st) {
-  __shared__ MergeSmem<16> sm;
-  const int tiles_x = (g.OW + MW - 1) / MW, n = tiles_x * ((g.OH + 15) / 16);
+  __shared__ MergeSmem<MH> sm;
+  const int tiles_x = (g.OW + MW - 1) / MW, n = tiles_x * ((g.OH + MH - 1) / MH);
   const int t = xcd_tile(blockIdx.x, n);
-  merge_tile<16, 256, TILE_STREAM, RB>(frames, motion, rmin, g, mc, nullptr, nullptr, st, t % tiles_x, t / tiles_x,
+  merge_tile<MH, 256, TILE_STREAM, RB>(frames, motion, rmin, g, mc, nullptr, nullptr, st, t % tiles_x, t / tiles_x,
                                    sm);
 }
 
@@ -52,17 +52,55 @@ __global__ void k_stream_finish(const float* __restrict__ state, size_t plane, f
     out[i + c * plane] = (state[i + c * plane] / state[i + (3 + c) * plane] - black) * inv_range;
 }
 
+dim3 tile_grid(const Geometry& g, int rows) { return dim3(((g.OW + MW - 1) / MW) * ((g.OH + rows - 1) / rows)); }
+
 template <int MH, int THREADS>
 hipError_t launch_variant(const Geometry& g, const MergeConsts& mc, const uint16_t* frames,
                           const float* motion, const float* rmin, float* out, hipStream_t stream) {
-  const dim3 grid(((g.OW + MW - 1) / MW) * ((g.OH + MH - 1) / MH));
   if (wide_raw_window(MH, THREADS, g.scale))
-    hipLaunchKernelGGL((k_merge<MH, THREADS, 8>), grid, dim3(THREADS), 0, stream, frames, motion, rmin, g,
+    hipLaunchKernelGGL((k_merge<MH, THREADS, 8>), tile_grid(g, MH), dim3(THREADS), 0, stream, frames, motion, rmin, g,
                        mc, out);
   else
-    hipLaunchKernelGGL((k_merge<MH, THREADS, 4>), grid, dim3(THREADS), 0, stream, frames, motion, rmin, g,
+    hipLaunchKernelGGL((k_merge<MH, THREADS, 4>), tile_grid(g, MH), dim3(THREADS), 0, stream, frames, motion, rmin, g,
                        mc, out);
   return hipGetLastError();
+}
+
+template <int MH>
+hipError_t launch_save(const Geometry& g, const MergeConsts& mc, const uint16_t* frames, const float* motion,
+                       const float* rmin, float* out, float* saved, hipStream_t stream) {
+  if (wide_raw_window(MH, 256, g.scale))
+    hipLaunchKernelGGL((k_merge_save<MH, 8>), tile_grid(g, MH), dim3(256), 0, stream, frames, motion, rmin, g, mc,
+                       out, saved);
+  else
+    hipLaunchKernelGGL((k_merge_save<MH, 4>), tile_grid(g, MH), dim3(256), 0, stream, frames, motion, rmin, g, mc,
+                       out, saved);
+  return hipGetLastError();
+}
+
+template <int MH>
+hipError_t launch_stream(const Geometry& g, const MergeConsts& mc, const uint16_t* frames, const float* motion,
+                         const float* rmin, StreamState st, hipStream_t stream) {
+  if (wide_raw_window(MH, 256, g.scale))
+    hipLaunchKernelGGL((k_merge_stream<MH, 8>), tile_grid(g, MH), dim3(256), 0, stream, frames, motion, rmin, g, mc,
+                       st);
+  else
+    hipLaunchKernelGGL((k_merge_stream<MH, 4>), tile_grid(g, MH), dim3(256), 0, stream, frames, motion, rmin, g, mc,
+                       st);
+  return hipGetLastError();
+}
+
+// Rows of the 64-column, 256-thread tile for an output: 16 where that fills
+// the 256 compute units, else fewer, so that more of them work and a frame's
+// chain (stage, Omega, one to four pixels a thread) is shorter. A pixel's
+// arithmetic does not depend on the shape: the results are the same bits.
+// Measured with 64 x 16 tiles / 64 x 8 / 64 x 4, us per merge: 8 x 256 x 256
+// (64 tiles of 64 x 16) 54.6 / 39.5 / 33.7, 8 x 384 x 512 (192) 57.5 / 48.5 /
+// 46.0, 8 x 256 x 256 at scale 2 (256) 51.1 / 44.9 / 47.0, 8 x 512 x 512 at
+// 1.5 (576) 75.9 / 75.3 / 82.6, 5 x 750 x 1002 at 1.5 (1704) 98 / 114 / 139.
+int small_tile_rows(const Geometry& g) {
+  const unsigned tiles = tile_grid(g, 16).x;
+  return tiles <= 192 ? 4 : (tiles <= 384 ? 8 : 16);
 }
 
 }  // namespace
@@ -75,17 +113,18 @@ const int kNumMergeVariants = sizeof(kMergeVariants) / sizeof(kMergeVariants[0])
 hipError_t launch_merge(int variant, const Geometry& g, const MergeConsts& mc, const uint16_t* frames,
                         const float* motion, const float* rmin, float* out, float* saved,
                         hipStream_t stream) {
-  if (saved) {  // one tile shape keeps the normaliser
-    const dim3 grid(((g.OW + MW - 1) / MW) * ((g.OH + 15) / 16));
-    if (wide_raw_window(16, 256, g.scale))
-      hipLaunchKernelGGL(k_merge_save<8>, grid, dim3(256), 0, stream, frames, motion, rmin, g, mc, out, saved);
-    else
-      hipLaunchKernelGGL(k_merge_save<4>, grid, dim3(256), 0, stream, frames, motion, rmin, g, mc, out, saved);
-    return hipGetLastError();
+  const int rows = small_tile_rows(g);
+  if (saved) {  // 64 columns, 256 threads keep the normaliser
+    if (rows == 4) return launch_save<4>(g, mc, frames, motion, rmin, out, saved, stream);
+    if (rows == 8) return launch_save<8>(g, mc, frames, motion, rmin, out, saved, stream);
+    return launch_save<16>(g, mc, frames, motion, rmin, out, saved, stream);
   }
   switch (variant) {
     case 1: return launch_variant<32, 512>(g, mc, frames, motion, rmin, out, stream);
-    case 2: return launch_variant<16, 256>(g, mc, frames, motion, rmin, out, stream);
+    case 2:
+      if (rows == 4) return launch_variant<4, 256>(g, mc, frames, motion, rmin, out, stream);
+      if (rows == 8) return launch_variant<8, 256>(g, mc, frames, motion, rmin, out, stream);
+      return launch_variant<16, 256>(g, mc, frames, motion, rmin, out, stream);
     case 3: return launch_variant<16, 128>(g, mc, frames, motion, rmin, out, stream);
     default: return launch_variant<32, 256>(g, mc, frames, motion, rmin, out, stream);
   }
@@ -100,14 +139,12 @@ int merge_tile_rows(int variant) { return kMergeVariants[variant].rows; }
 hipError_t launch_merge_stream(const Geometry& g, const MergeConsts& mc, const uint16_t* frames,
                                const float* motion, const float* rmin, const float* state_in, float* state_out,
                                int first, hipStream_t stream) {
-  const dim3 grid(((g.OW + MW - 1) / MW) * ((g.OH + 15) / 16));
-  if (wide_raw_window(16, 256, g.scale))
-    hipLaunchKernelGGL(k_merge_stream<8>, grid, dim3(256), 0, stream, frames, motion, rmin, g, mc,
-                       StreamState{state_in, state_out, first});
-  else
-    hipLaunchKernelGGL(k_merge_stream<4>, grid, dim3(256), 0, stream, frames, motion, rmin, g, mc,
-                       StreamState{state_in, state_out, first});
-  return hipGetLastError();
+  const StreamState st{state_in, state_out, first};
+  switch (small_tile_rows(g)) {
+    case 4: return launch_stream<4>(g, mc, frames, motion, rmin, st, stream);
+    case 8: return launch_stream<8>(g, mc, frames, motion, rmin, st, stream);
+    default: return launch_stream<16>(g, mc, frames, motion, rmin, st, stream);
+  }
 }
 
 hipError_t launch_stream_finish(const Geometry& g, const MergeConsts& mc, const float* state, float* out,
