@@ -388,7 +388,7 @@ hmfsr_status hmfsr_merge_maps(const hmfsr_desc* desc, const hmfsr_tuning* tuning
  *  frames, motion, out
  *                  HOST arrays [n_bursts] of DEVICE pointers with the
  *                  layouts of hmfsr_merge.
- * The graph holds a counter reset, the motion prior of every burst, one
+ * The graph holds the motion prior and guide statistics of every burst, one
  * persistent robustness kernel and one persistent merge kernel per tile
  * shape; persistent workgroups take (burst, tile) items from a global counter,
  * most expensive bursts first. The first call for a set of shapes and buffers

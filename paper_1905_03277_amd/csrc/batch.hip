@@ -3,8 +3,8 @@
 //
 // hmfsr_merge_batch lays out one workspace for every burst (rejection
 // strengths, R_hat), per-burst argument blocks and cost-ordered work lists,
-// then records into a hipGraph: a counter reset, the motion prior of every
-// (burst, frame, tile), the guide statistics, one persistent robustness
+// then records into a hipGraph: the motion prior and guide statistics of every
+// burst (and the counters' reset), one persistent robustness
 // launch over all (burst, tile) items and one persistent merge launch per
 // class (tile shape, raw-load batch size), each with an XCD-chunked queue. The graph is
 // kept and replayed while the bursts' shapes and buffers stay the same;
@@ -283,15 +283,17 @@ hmfsr_status hmfsr_merge_batch(int32_t n_bursts, const hmfsr_desc* descs, const 
   // same shapes and buffers as the captured graph: refresh arguments, replay
   // (descriptors and tunings are plain int32 / float structs: memcmp is exact)
   std::vector<const void*> ptrs;
+  bool any_hf = false;
   for (int i = 0; i < n_bursts; ++i) {
     ptrs.push_back(frames[i]);
     ptrs.push_back(motion[i]);
     ptrs.push_back(out[i]);
+    any_hf = any_hf || tunings[i].hf_ratio > 0.f;
   }
   BatchPlan& P = ds.plan;
   const int cap = batch_groups_cap();
   const bool same = P.exec && P.ws == ds.batch_ws && P.variants == var && P.ptrs == ptrs && P.groups_cap == cap &&
-                    P.descs.size() == (size_t)n_bursts &&
+                    (P.any_hf || !any_hf) && P.descs.size() == (size_t)n_bursts &&
                     memcmp(P.descs.data(), descs, sizeof(hmfsr_desc) * n_bursts) == 0;
   if (same) {
     if (memcmp(P.tunings.data(), tunings, sizeof(hmfsr_tuning) * n_bursts) != 0) {
@@ -378,10 +380,8 @@ hmfsr_status hmfsr_merge_batch(int32_t n_bursts, const hmfsr_desc* descs, const 
   hipStream_t cs = ds.capture_stream;
   hipGraph_t graph = nullptr;
   if (hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) != hipSuccess) return HMFSR_E_HIP;
-  hipError_t err = launch_fill_i32(d_counters, 0, kQueues * XCDS, cs);
-  if (err == hipSuccess) err = launch_prior_batch(d_args, d_first, n_bursts, (int)n_prior, cs);
-  if (err == hipSuccess)
-    err = launch_guide_stats_batch(d_args, d_bfirst, (int)n_base, d_ffirst, (int)n_fmeans, n_bursts, cs);
+  hipError_t err = launch_guide_batch(d_args, n_bursts, d_ffirst, (int)n_fmeans, d_bfirst, (int)n_base, d_first,
+                                      (int)n_prior, any_hf, d_counters, kQueues * XCDS, cs);
   hmfsr_batch_info info = {};
   if (err == hipSuccess && n_ritems) {
     const int groups = capped(n_ritems, (size_t)cus * robust_batch_blocks_per_cu(), cap);
@@ -415,6 +415,7 @@ hmfsr_status hmfsr_merge_batch(int32_t n_bursts, const hmfsr_desc* descs, const 
   P.variants = var;
   P.ptrs = ptrs;
   P.descs.assign(descs, descs + n_bursts);
+  P.any_hf = any_hf;
   P.tunings.assign(tunings, tunings + n_bursts);
   P.groups_cap = cap;
   P.info = info;

@@ -124,15 +124,15 @@ hipError_t launch_merge_batch(int cls, const BurstArgs* bursts, const WorkItem* 
                               int* counters, int n_groups, hipStream_t stream);
 hipError_t launch_robust_batch(const BurstArgs* bursts, const WorkItem* items, const int* bounds,
                                int* counters, int n_groups, hipStream_t stream);
-// Guide statistics of every burst of a batch, the base frames' and the aligned
-// frames' in two flat launches: workgroup i belongs to the last burst b with
-// first[b] <= i (first[b] = the workgroups of the bursts before b).
-hipError_t launch_guide_stats_batch(const BurstArgs* bursts, const int* base_first, int base_total,
-                                    const int* frame_first, int frame_total, int n_bursts, hipStream_t stream);
+// Prior and guide statistics of every burst of a batch in one launch, which
+// also sets `counters` to 0. Workgroup i of a part (flat tile i of the prior)
+// belongs to the last burst b with first[b] <= i (first[b] = the workgroups,
+// or tiles, of the bursts before b). any_hf: some burst has hf_ratio > 0.
+hipError_t launch_guide_batch(const BurstArgs* bursts, int n_bursts, const int* mfirst, int n_means,
+                              const int* bfirst, int n_base, const int* pfirst, int n_prior, bool any_hf,
+                              int* counters, int n_counters, hipStream_t stream);
 int base_stats_groups(const Geometry& g);
 int frame_means_groups(const Geometry& g);
-hipError_t launch_prior_batch(const BurstArgs* bursts, const int* first, int n_bursts, int total,
-                              hipStream_t stream);
 int merge_tile_rows(int variant);
 // Streaming merge (64 x 16 tiles): frames from loop index `first` on are added
 // to the accumulator state [9][OH][OW] (numerator, denominator, reference
@@ -146,7 +146,6 @@ int merge_batch_blocks_per_cu(int cls);
 int robust_batch_blocks_per_cu();
 int robust_tiles_x(const Geometry& g);
 int robust_tiles_y(const Geometry& g);
-hipError_t launch_fill_i32(int* p, int v, size_t n, hipStream_t stream);
 hipError_t launch_fill(float* p, float v, size_t n, hipStream_t stream);
 hipError_t launch_omega_map(const Geometry& g, const OmegaConsts& oc, const uint16_t* frames,
                             double* omega, hipStream_t stream);

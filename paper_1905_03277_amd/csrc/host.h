@@ -14,6 +14,7 @@ constexpr int kMaxDevices = 64;
 struct BatchPlan {
   std::vector<hmfsr_desc> descs;
   std::vector<const void*> ptrs;  // frames, motion, out of every burst
+  bool any_hf = false;            // the statistics' launch has LDS for S.3
   std::vector<int> variants;
   void* ws = nullptr;             // batch workspace the graph's arguments point into
   std::vector<hmfsr_tuning> tunings;  // the tunings of the uploaded argument blocks

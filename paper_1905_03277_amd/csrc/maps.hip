@@ -17,23 +17,6 @@ __global__ void k_prior(const float* __restrict__ motion, Geometry g, PriorConst
   prior_one(motion, g, pc, s_tile, mov, blockIdx.z, ty, tx);
 }
 
-// Every (burst, frame, tile) of a batch; first[b] = first flat index of burst b.
-__global__ void k_prior_batch(const BurstArgs* __restrict__ bursts, const int* __restrict__ first,
-                              int n_bursts, int total) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  int lo = 0, hi = n_bursts - 1;  // last burst with first[b] <= i
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (first[mid] <= i) lo = mid; else hi = mid - 1;
-  }
-  const BurstArgs& b = bursts[lo];
-  const int k = i - first[lo];
-  const int per = b.g.TY * b.g.TX;
-  const int n = k / per, t = k - n * per;
-  prior_one(b.motion, b.g, b.pc, b.s_tile, b.mov, n, t / b.g.TX, t % b.g.TX);
-}
-
 // Omega per half-res pixel of every frame (inspection output).
 __global__ void k_omega_map(const uint16_t* __restrict__ frames, Geometry g, OmegaConsts oc,
                             double* __restrict__ omega) {
@@ -63,18 +46,7 @@ __global__ void k_fill(float* __restrict__ p, float v, size_t n) {
   if (i < n) p[i] = v;
 }
 
-__global__ void k_fill_i32(int* __restrict__ p, int v, size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
-}
-
 }  // namespace
-
-hipError_t launch_fill_i32(int* p, int v, size_t n, hipStream_t stream) {
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, p, v, n);
-  return hipGetLastError();
-}
 
 hipError_t launch_fill(float* p, float v, size_t n, hipStream_t stream) {
   if (n == 0) return hipSuccess;
@@ -114,14 +86,6 @@ hipError_t launch_prior(const Geometry& g, const PriorConsts& pc, const float* m
   const dim3 blk(16, 16);
   const dim3 grid((g.TX + 15) / 16, (g.TY + 15) / 16, g.n);
   hipLaunchKernelGGL(k_prior, grid, blk, 0, stream, motion, g, pc, w.s_tile, w.mov);
-  return hipGetLastError();
-}
-
-hipError_t launch_prior_batch(const BurstArgs* bursts, const int* first, int n_bursts, int total,
-                              hipStream_t stream) {
-  if (total == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_prior_batch, dim3((total + 255) / 256), dim3(256), 0, stream, bursts, first,
-                     n_bursts, total);
   return hipGetLastError();
 }
 

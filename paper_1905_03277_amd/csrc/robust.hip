@@ -183,19 +183,6 @@ __global__ __launch_bounds__(THREADS) void k_frame_means(const uint16_t* __restr
   frame_means_block(frames, g, gmu, n, t % ns, (t / ns) * FM_WAVES + (threadIdx.x >> 6));
 }
 
-// Every (burst, aligned frame, strip, band) of a batch, one workgroup each;
-// each XCD takes a contiguous run of the flat list (neighbours share an L2).
-__global__ __launch_bounds__(THREADS) void k_frame_means_batch(const BurstArgs* __restrict__ bursts,
-                                                               const int* __restrict__ first, int n_bursts,
-                                                               int total) {
-  const int i = xcd_tile(blockIdx.x, total), bi = burst_of(first, n_bursts, i);
-  const BurstArgs& b = bursts[bi];
-  const int ns = fm_strips(b.g), per = ns * fm_bands(b.g);
-  const int k = i - first[bi], m = k / per, t = k - m * per;
-  const int n = m < b.g.ref ? m : m + 1;
-  frame_means_block(b.frames, b.g, b.gmu, n, t % ns, (t / ns) * FM_WAVES + (threadIdx.x >> 6));
-}
-
 // ---- pass 1b: the base frame's statistics ------------------------------------------
 struct BaseSmem {
   float G[3][GW_N];  // guide at rows I0-2 .. I0+GM_H+1, columns J0-2 .., clamped to the grid
@@ -370,15 +357,45 @@ __global__ __launch_bounds__(THREADS) void k_guide(const uint16_t* __restrict__ 
   prior_one(motion, g, pc, s_tile, mov, n, t / g.TX, t % g.TX);
 }
 
-// Every (burst, tile) of a batch, one workgroup each, in XCD-contiguous runs.
-__global__ __launch_bounds__(THREADS) void k_base_stats_batch(const BurstArgs* __restrict__ bursts,
-                                                              const int* __restrict__ first, int n_bursts,
-                                                              int total) {
-  __shared__ BaseSmem sm;
-  const int i = xcd_tile(blockIdx.x, total), bi = burst_of(first, n_bursts, i);
-  const BurstArgs& b = bursts[bi];
-  const int tx_n = means_tiles_x(b.g), t = i - first[bi];
-  base_stats_tile(b.frames, b.g, b.rc, b.gmu, b.gref, t % tx_n, t / tx_n, sm);
+// The same for every burst of a batch, each part a flat list over the bursts
+// (mfirst, bfirst, pfirst: the first workgroup, or flat tile index, of each
+// burst; see burst_of) in XCD-contiguous runs; the first workgroup also resets
+// the item counters of the launches that follow.
+__global__ __launch_bounds__(THREADS) void k_guide_batch(const BurstArgs* __restrict__ bursts, int n_bursts,
+                                                         const int* __restrict__ mfirst, int n_means,
+                                                         const int* __restrict__ bfirst, int n_base,
+                                                         const int* __restrict__ pfirst, int n_prior,
+                                                         int* __restrict__ counters, int n_counters) {
+  extern __shared__ float dyn[];
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < n_counters; i += THREADS) counters[i] = 0;
+  const int n_means8 = (n_means + XCDS - 1) / XCDS * XCDS, n_base8 = (n_base + XCDS - 1) / XCDS * XCDS;
+  int b = blockIdx.x;
+  if (b < n_means8) {
+    if (b >= n_means) return;
+    const int i = xcd_tile(b, n_means), bi = burst_of(mfirst, n_bursts, i);
+    const BurstArgs& a = bursts[bi];
+    const int ns = fm_strips(a.g), per = ns * fm_bands(a.g);
+    const int k = i - mfirst[bi], m = k / per, t = k - m * per;
+    frame_means_block(a.frames, a.g, a.gmu, m < a.g.ref ? m : m + 1, t % ns,
+                      (t / ns) * FM_WAVES + (threadIdx.x >> 6));
+    return;
+  }
+  b -= n_means8;
+  if (b < n_base8) {
+    if (b >= n_base) return;
+    const int i = xcd_tile(b, n_base), bi = burst_of(bfirst, n_bursts, i);
+    const BurstArgs& a = bursts[bi];
+    const int tx_n = means_tiles_x(a.g), t = i - bfirst[bi];
+    base_stats_tile(a.frames, a.g, a.rc, a.gmu, a.gref, t % tx_n, t / tx_n, *(BaseSmem*)dyn);
+    return;
+  }
+  const int i = (b - n_base8) * THREADS + threadIdx.x;
+  if (i >= n_prior) return;
+  const int bi = burst_of(pfirst, n_bursts, i);
+  const BurstArgs& a = bursts[bi];
+  const int k = i - pfirst[bi], per = a.g.TY * a.g.TX, n = k / per, t = k - n * per;
+  prior_one(a.motion, a.g, a.pc, a.s_tile, a.mov, n, t / a.g.TX, t % a.g.TX);
 }
 
 // ---- pass 2: robustness and its 5x5 minimum ---------------------------------------
@@ -703,17 +720,15 @@ hipError_t launch_robust(const Geometry& g, const RobustConsts& rc, const float*
   return hipGetLastError();
 }
 
-hipError_t launch_guide_stats_batch(const BurstArgs* bursts, const int* base_first, int base_total,
-                                    const int* frame_first, int frame_total, int n_bursts, hipStream_t stream) {
-  if (base_total > 0) {
-    hipLaunchKernelGGL(k_base_stats_batch, dim3(base_total), dim3(THREADS), 0, stream, bursts, base_first,
-                       n_bursts, base_total);
-    const hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
-  }
-  if (frame_total > 0)
-    hipLaunchKernelGGL(k_frame_means_batch, dim3(frame_total), dim3(THREADS), 0, stream, bursts, frame_first,
-                       n_bursts, frame_total);
+hipError_t launch_guide_batch(const BurstArgs* bursts, int n_bursts, const int* mfirst, int n_means,
+                              const int* bfirst, int n_base, const int* pfirst, int n_prior, bool any_hf,
+                              int* counters, int n_counters, hipStream_t stream) {
+  auto up8 = [](int v) { return (v + XCDS - 1) / XCDS * XCDS; };
+  const unsigned groups = (unsigned)up8(n_means) + (unsigned)up8(n_base) + (unsigned)((n_prior + THREADS - 1) / THREADS);
+  RobustConsts rc = {};
+  rc.hf = any_hf ? 1.0 : 0.0;
+  hipLaunchKernelGGL(k_guide_batch, dim3(groups), dim3(THREADS), base_smem_bytes(rc), stream, bursts, n_bursts, mfirst,
+                     n_means, bfirst, n_base, pfirst, n_prior, counters, n_counters);
   return hipGetLastError();
 }
 
