@@ -391,10 +391,11 @@ hmfsr_status hmfsr_merge_maps(const hmfsr_desc* desc, const hmfsr_tuning* tuning
  * The graph holds the motion prior and guide statistics of every burst, one
  * persistent robustness kernel and one persistent merge kernel per tile
  * shape; persistent workgroups take (burst, tile) items from a global counter,
- * most expensive bursts first. The first call for a set of shapes and buffers
- * builds and instantiates the graph (synchronising `stream` once); later calls
- * with the same descriptors and pointers replay it, uploading changed tuning
- * values first (after synchronising `stream`). Results equal hmfsr_merge's
+ * most expensive bursts first. The first call for a set of shapes builds and
+ * instantiates the graph (synchronising `stream` once); later calls with the
+ * same descriptors replay it, writing changed buffer addresses (in stream
+ * order) and uploading changed tuning values (after synchronising `stream`)
+ * first. Results equal hmfsr_merge's
  * for the same tile shape bit for bit.
  */
 hmfsr_status hmfsr_merge_batch(int32_t n_bursts, const hmfsr_desc* descs,

@@ -131,6 +131,8 @@ hipError_t launch_robust_batch(const BurstArgs* bursts, const WorkItem* items, c
 hipError_t launch_guide_batch(const BurstArgs* bursts, int n_bursts, const int* mfirst, int n_means,
                               const int* bfirst, int n_base, const int* pfirst, int n_prior, bool any_hf,
                               int* counters, int n_counters, hipStream_t stream);
+// Each burst's buffers into its argument block, in stream order.
+hipError_t launch_set_buffers(BurstArgs* bursts, int n_bursts, const BurstArgs* host_args, hipStream_t stream);
 int base_stats_groups(const Geometry& g);
 int frame_means_groups(const Geometry& g);
 int merge_tile_rows(int variant);

@@ -12,8 +12,8 @@ constexpr int kMaxDevices = 64;
 
 // A captured batch graph and the signature it was built for.
 struct BatchPlan {
-  std::vector<hmfsr_desc> descs;
-  std::vector<const void*> ptrs;  // frames, motion, out of every burst
+  std::vector<hmfsr_desc> descs;  // noise tables' addresses cleared
+  std::vector<const void*> ptrs;  // frames, motion, out, noise table of every burst, as the argument blocks hold them
   bool any_hf = false;            // the statistics' launch has LDS for S.3
   std::vector<int> variants;
   void* ws = nullptr;             // batch workspace the graph's arguments point into
