@@ -433,11 +433,11 @@ hmfsr_status hmfsr_merge_backward(const hmfsr_desc* desc, const hmfsr_tuning* tu
       }) != hipSuccess)
     return HMFSR_E_HIP;
   if (timed(HMFSR_STAGE_ROBUST_BWD, s, [&] {
-        return launch_robust_bwd(g, rc, pc, bc, frames, motion, w, s);
+        return launch_robust_bwd(g, rc, pc, bc, motion, w, grad_motion, s);
       }) != hipSuccess)
     return HMFSR_E_HIP;
   if (timed(HMFSR_STAGE_GRAD_REDUCE, s, [&] {
-        return launch_grad_reduce(g, bc, w, grad_tuning, grad_motion, s);
+        return launch_grad_tuning(g, bc, w, grad_tuning, s);
       }) != hipSuccess)
     return HMFSR_E_HIP;
   return HMFSR_OK;

@@ -174,8 +174,9 @@ struct BwdWork {
   float* part_rh;     // [n][tiles][kBwdRH] dL/dR_hat over each tile's R_hat window
   double* part_mo;    // [tiles][n][kBwdVT][2] dL/dv of the alignment tiles each tile touches
   double* part_theta; // [tiles][6] dL/d(k_detail, k_denoise, d_th, d_tr, k_stretch, k_shrink), unscaled
-  double* part_rob;   // [n][TY][TX][5] robustness part: dL/dvx, dL/dvy, dL/dt, dL/ds, dL/ds_motion
+  double* part_rob;   // [n][TY][TX][3] robustness part: dL/dt, dL/ds, dL/ds_motion
   double* part_sum;   // [64][9] chunk sums of the tuning gradient
+  int* ticket;        // workgroups of that sum that have finished; set to 0 by the robustness adjoint
 };
 size_t bwd_bytes(const Geometry& g, bool need_saved);
 BwdWork bwd_carve(void* base, const Geometry& g, bool need_saved);
@@ -184,11 +185,12 @@ hipError_t launch_merge_bwd(const Geometry& g, const MergeConsts& mc, const BwdC
                             const uint16_t* frames, const float* motion, const float* rmin,
                             const float* saved, const float* grad_out, const BwdWork& w,
                             hipStream_t stream);
+// The robustness adjoint; also adds up the motion gradient.
 hipError_t launch_robust_bwd(const Geometry& g, const RobustConsts& rc, const PriorConsts& pc,
-                             const BwdConsts& bc, const uint16_t* frames, const float* motion,
-                             const BwdWork& w, hipStream_t stream);
-hipError_t launch_grad_reduce(const Geometry& g, const BwdConsts& bc, const BwdWork& w,
-                              float* grad_tuning, float* grad_motion, hipStream_t stream);
+                             const BwdConsts& bc, const float* motion, const BwdWork& w, float* grad_motion,
+                             hipStream_t stream);
+hipError_t launch_grad_tuning(const Geometry& g, const BwdConsts& bc, const BwdWork& w, float* grad_tuning,
+                              hipStream_t stream);
 
 // ---- tile alignment ----------------------------------------------------------
 
