@@ -523,22 +523,23 @@ hmfsr_status hmfsr_auto_tuning(const hmfsr_desc* desc, const uint16_t* frames, h
   if (st != HMFSR_OK) return st;
   if (!frames || ((uintptr_t)frames & 3) || !tuning) return HMFSR_E_INVALID;
   unsigned long long total = 0;
+  const long long n_px = (long long)desc->height * desc->width;
   {
     std::lock_guard<std::mutex> lock(g_mutex);
     int dev = 0;
     if ((st = current_device(&dev)) != HMFSR_OK) return st;
     hipStream_t s = (hipStream_t)stream;
-    void* ws = nullptr;
     DeviceState& ds = g_dev[dev];
-    if ((st = grow_buffer(ds.sum_ws, ds.sum_ws_bytes, (kFrameSumGroups + 1) * sizeof(unsigned long long), s, &ws)) !=
-        HMFSR_OK)
-      return st;
-    unsigned long long* parts = (unsigned long long*)ws;
-    const long long n = (long long)desc->height * desc->width;
-    if (launch_frame_sum(frames + (size_t)desc->ref_frame * n, n, parts, parts + kFrameSumGroups, s) != hipSuccess ||
-        hipMemcpyAsync(&total, parts + kFrameSumGroups, sizeof(total), hipMemcpyDeviceToHost, s) != hipSuccess ||
+    if (!ds.sum_host &&
+        hipHostMalloc((void**)&ds.sum_host, kFrameSumGroups * sizeof(unsigned long long), 0) != hipSuccess) {
+      (void)hipGetLastError();
+      ds.sum_host = nullptr;
+      return HMFSR_E_NOMEM;
+    }
+    if (launch_frame_sum(frames + (size_t)desc->ref_frame * n_px, n_px, ds.sum_host, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
       return HMFSR_E_HIP;
+    for (int i = 0; i < frame_sum_groups(n_px); ++i) total += ds.sum_host[i];
   }
   // SNR at the mean brightness, rounded operation by operation (one statement
   // per operation: no contraction)
@@ -628,7 +629,7 @@ void hmfsr_release(void) {
   const bool have_cur = hipGetDevice(&cur) == hipSuccess;
   for (int d = 0; d < kMaxDevices; ++d) {
     DeviceState& st = g_dev[d];
-    if (!st.workspace && !st.batch_ws && !st.bwd_ws && !st.stream_ws && !st.align_ws && !st.sum_ws && !st.debug_ws &&
+    if (!st.workspace && !st.batch_ws && !st.bwd_ws && !st.stream_ws && !st.align_ws && !st.sum_host && !st.debug_ws &&
         !st.plan.exec && !st.capture_stream)
       continue;
     if (hipSetDevice(d) != hipSuccess) continue;
@@ -644,9 +645,8 @@ void hmfsr_release(void) {
     if (st.align_ws) (void)hipFree(st.align_ws);
     st.align_ws = nullptr;
     st.align_ws_bytes = 0;
-    if (st.sum_ws) (void)hipFree(st.sum_ws);
-    st.sum_ws = nullptr;
-    st.sum_ws_bytes = 0;
+    if (st.sum_host) (void)hipHostFree(st.sum_host);
+    st.sum_host = nullptr;
     if (st.debug_ws) (void)hipFree(st.debug_ws);
     st.debug_ws = nullptr;
     st.debug_ws_bytes = 0;

@@ -108,7 +108,7 @@ struct MergeVariant {
 extern const MergeVariant kMergeVariants[];
 extern const int kNumMergeVariants;
 // out and saved are each nullable. saved receives the normaliser of eq. (1),
-// accumulated in float64 (the 64 x 16 tile shape is then used): three float64
+// accumulated in float64 (the default tile shape is then used): three float64
 // planes C per channel (raw units), then three float32 planes of the
 // denominator and three of the reference exponent (12 4-byte words per pixel).
 hipError_t launch_merge(int variant, const Geometry& g, const MergeConsts& mc, const uint16_t* frames,
@@ -223,10 +223,10 @@ hipError_t launch_align(const AlignGeom& ag, const uint16_t* frames, int H, int 
 // Monte-Carlo noise table into `table` [bins][4] (float32).
 hipError_t launch_noise_table(double a, double b, double lo, int bins, int patches, unsigned long long seed,
                               float* table, hipStream_t stream);
-// Sum of one frame's raw values into *sum (device, one 64-bit word); `parts`
-// holds one word per workgroup of the first pass (at most kFrameSumGroups).
+// Partial sums of one frame's n raw values, one word per workgroup
+// (frame_sum_groups(n) of them, at most kFrameSumGroups).
 constexpr int kFrameSumGroups = 1024;
-hipError_t launch_frame_sum(const uint16_t* frame, long long n, unsigned long long* parts,
-                            unsigned long long* sum, hipStream_t stream);
+int frame_sum_groups(long long n);
+hipError_t launch_frame_sum(const uint16_t* frame, long long n, unsigned long long* parts, hipStream_t stream);
 
 }  // namespace hmfsr

@@ -37,8 +37,7 @@ struct DeviceState {
   size_t stream_ws_bytes = 0;
   void* align_ws = nullptr;   // tile alignment: pyramids and block vectors
   size_t align_ws_bytes = 0;
-  void* sum_ws = nullptr;     // frame sums for the SNR-dependent tuning
-  size_t sum_ws_bytes = 0;
+  unsigned long long* sum_host = nullptr;  // pinned: partial frame sums for the SNR-dependent tuning
   void* debug_ws = nullptr;   // HMFSR_DEBUG: the device checks' result word
   size_t debug_ws_bytes = 0;
   hipStream_t capture_stream = nullptr;

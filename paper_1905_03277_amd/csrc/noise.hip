@@ -101,7 +101,10 @@ __global__ __launch_bounds__(kThreads) void k_noise_table(double a, double b, do
 }
 
 // Exact sum of n uint16 values (n even, 4-byte aligned): per-workgroup partial
-// sums in a grid-stride loop over 32-bit pairs, then one workgroup adds them.
+// sums in a grid-stride loop over 32-bit pairs, written to host memory, where
+// the host adds them (integers: exact in any order). A second launch that
+// added them and a copy of its result cost more than the sum: the SNR of a
+// 3 MP frame took 40 us on the host's clock, now 27.
 __global__ __launch_bounds__(kThreads) void k_frame_sum(const uint32_t* __restrict__ pairs, long long n_pairs,
                                                         unsigned long long* __restrict__ parts) {
   __shared__ unsigned long long red[kThreads / 64];
@@ -125,20 +128,6 @@ __global__ __launch_bounds__(kThreads) void k_frame_sum(const uint32_t* __restri
   }
 }
 
-// One wave adds the partial sums (integers: exact in any order).
-__global__ __launch_bounds__(64) void k_sum_parts(const unsigned long long* __restrict__ parts, int n,
-                                                  unsigned long long* __restrict__ sum) {
-  unsigned long long t = 0;
-  for (int i = threadIdx.x; i < n; i += 64) t += parts[i];
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const unsigned lo = __shfl_xor((unsigned)(t & 0xffffffffull), off, 64);
-    const unsigned hi = __shfl_xor((unsigned)(t >> 32), off, 64);
-    t += ((unsigned long long)hi << 32) | lo;
-  }
-  if (threadIdx.x == 0) *sum = t;
-}
-
 }  // namespace
 
 hipError_t launch_noise_table(double a, double b, double lo, int bins, int patches, unsigned long long seed,
@@ -148,15 +137,14 @@ hipError_t launch_noise_table(double a, double b, double lo, int bins, int patch
   return hipGetLastError();
 }
 
-hipError_t launch_frame_sum(const uint16_t* frame, long long n, unsigned long long* parts, unsigned long long* sum,
-                            hipStream_t stream) {
-  const long long n_pairs = n / 2;
-  const long long want = (n_pairs + kThreads * 8 - 1) / (kThreads * 8);
-  const int groups = (int)(want < 1 ? 1 : (want > kFrameSumGroups ? kFrameSumGroups : want));
-  hipLaunchKernelGGL(k_frame_sum, dim3(groups), dim3(kThreads), 0, stream, (const uint32_t*)frame, n_pairs, parts);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(64), 0, stream, parts, groups, sum);
+int frame_sum_groups(long long n) {
+  const long long want = (n / 2 + kThreads * 8 - 1) / (kThreads * 8);
+  return (int)(want < 1 ? 1 : (want > kFrameSumGroups ? kFrameSumGroups : want));
+}
+
+hipError_t launch_frame_sum(const uint16_t* frame, long long n, unsigned long long* parts, hipStream_t stream) {
+  hipLaunchKernelGGL(k_frame_sum, dim3(frame_sum_groups(n)), dim3(kThreads), 0, stream, (const uint32_t*)frame, n / 2,
+                     parts);
   return hipGetLastError();
 }
 
