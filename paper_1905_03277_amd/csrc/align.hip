@@ -847,7 +847,7 @@ template <int WIN>
 __global__ __launch_bounds__(256, 3) void k_align_lk_cols(const int32_t* __restrict__ pyr,
                                                           const int2* __restrict__ vecs, LkArgs a,
                                                           float2* __restrict__ motion, int2* __restrict__ bm_out,
-                                                          int per_frame, int passes, int chunk) {
+                                                          int n_aligned, int per_frame, int passes, int chunk) {
   constexpr int TPW = 64 / WIN, RC = 2;  // tiles per wave; rows loaded together
   __shared__ double tables[kWaves][TPW * 24];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -857,28 +857,29 @@ __global__ __launch_bounds__(256, 3) void k_align_lk_cols(const int32_t* __restr
   const int gw = xcd_tile(blockIdx.x, gridDim.x) * (blockDim.x >> 6) + wave;
   const int p0 = gw * chunk, p1 = min(passes, p0 + chunk);
   const __amdgpu_buffer_rsrc_t rs_base = words_rsrc(pyr + (long long)a.ref * a.fstride, (long long)h * w);
+  // passes run over the aligned frames (over the base frame of a burst of one)
+  auto frame_of = [&](int m) { return n_aligned == 0 ? a.ref : m < a.ref ? m : m + 1; };
   // a pass's block-matching vectors are loaded one pass ahead
   auto load_bm = [&](int p) {
-    const int f = p / per_frame, t = min((p - f * per_frame) * TPW + g, per - 1);
-    return f == a.ref ? make_int2(0, 0) : vecs[(long long)f * a.vstride + a.voff0 + t];
+    const int m = p / per_frame, t = min((p - m * per_frame) * TPW + g, per - 1);
+    return n_aligned == 0 ? make_int2(0, 0) : vecs[(long long)frame_of(m) * a.vstride + a.voff0 + t];
   };
   int2 next_bm = make_int2(0, 0);
   if (p0 < p1) next_bm = load_bm(p0);
   for (int p = p0; p < p1; ++p) {
-    const int f = p / per_frame;  // uniform
-    const int t0 = (p - f * per_frame) * TPW + g;
+    const int m = p / per_frame, f = frame_of(m);  // uniform
+    const int t0 = (p - m * per_frame) * TPW + g;
     const bool valid = t0 < per;
     const int t = valid ? t0 : per - 1;
     const long long item = (long long)f * per + t;
     const int2 bm = next_bm;
     if (p + 1 < p1) next_bm = load_bm(p + 1);
-    if (f == a.ref) {
-      if (valid && l == 0) {
-        motion[item] = make_float2(0.f, 0.f);
-        if (bm_out) bm_out[item] = make_int2(0, 0);
-      }
-      continue;
+    if (m == 0 && valid && l == 0) {  // the base frame's vector of the same tile
+      const long long base = (long long)a.ref * per + t;
+      motion[base] = make_float2(0.f, 0.f);
+      if (bm_out) bm_out[base] = make_int2(0, 0);
     }
+    if (n_aligned == 0) continue;
     const __amdgpu_buffer_rsrc_t rs = words_rsrc(pyr + (long long)f * a.fstride, (long long)h * w);
     const int ty = t / a.TX, tx = t - ty * a.TX;
     const int wy0 = max(0, ty * a.B - a.m), WH = min(ty * a.B + a.B + a.m, h) - wy0;
@@ -1035,16 +1036,20 @@ hipError_t lk_cols(const int32_t* pyr, const int2* vecs, const LkArgs& a, int n,
                    int* block_match, hipStream_t stream) {
   constexpr int TPW = 64 / WIN;
   const int per_frame = (a.TY * a.TX + TPW - 1) / TPW;
-  const long long passes = (long long)n * per_frame;
-  // about eight rounds of the resident waves (three per SIMD), so that runs of
-  // tiles with far-apart vectors, whose loads miss the caches, even out (one
-  // round: 12 MP x 8 alignment 0.57 ms, eight 0.48 ms, one pass per wave 0.50)
-  const long long waves_wanted = (long long)cus * 12 * 8;
+  // The aligned frames only: as passes of their own, the base frame's left the
+  // XCD whose run they were without work (12 MP x 8 alignment 0.485 -> 0.450
+  // ms, this kernel at 3 MP x 8 93 -> 82 us).
+  const long long passes = (long long)std::max(n - 1, 1) * per_frame;
+  // about twelve rounds of the resident waves (three per SIMD), so that runs of
+  // tiles with far-apart vectors, whose loads miss the caches, even out (12 MP
+  // x 8 alignment with four / six / eight / twelve rounds and one pass per
+  // wave: 0.454 / 0.450 / 0.450 / 0.445 / 0.453 ms)
+  const long long waves_wanted = (long long)cus * 12 * 12;
   const long long chunk = (passes + waves_wanted - 1) / waves_wanted;
   const int waves = passes >= 4ll * cus ? kWaves : 1;  // few passes spread over more compute units
   const unsigned groups = (unsigned)(((passes + chunk - 1) / chunk + waves - 1) / waves);
   hipLaunchKernelGGL(k_align_lk_cols<WIN>, dim3(groups), dim3(64 * waves), 0, stream, pyr, vecs, a, (float2*)motion,
-                     (int2*)block_match, per_frame, (int)passes, (int)chunk);
+                     (int2*)block_match, n - 1, per_frame, (int)passes, (int)chunk);
   return hipGetLastError();
 }
 
