@@ -12,7 +12,7 @@ __global__ __launch_bounds__(THREADS, (waves_per_simd<MH, THREADS>())) void k_me
     const float* __restrict__ rmin, Geometry g, MergeConsts mc, float* __restrict__ out) {
   __shared__ MergeSmem<MH> sm;
   const int tiles_x = (g.OW + MW - 1) / MW, n = tiles_x * ((g.OH + MH - 1) / MH);
-  const int t = xcd_tile(blockIdx.x, n);
+  const int t = xcd_tile_runs<8>(blockIdx.x, n);
   merge_tile<MH, THREADS, TILE_PLAIN, RB>(frames, motion, rmin, g, mc, out, nullptr, StreamState{nullptr, nullptr, 0},
                                       t % tiles_x, t / tiles_x, sm);
 }
@@ -25,7 +25,7 @@ __global__ __launch_bounds__(256, 2) void k_merge_save(
     float* __restrict__ saved) {
   __shared__ MergeSmem<MH> sm;
   const int tiles_x = (g.OW + MW - 1) / MW, n = tiles_x * ((g.OH + MH - 1) / MH);
-  const int t = xcd_tile(blockIdx.x, n);
+  const int t = xcd_tile_runs<8>(blockIdx.x, n);
   merge_tile<MH, 256, TILE_SAVE, RB>(frames, motion, rmin, g, mc, out, saved, StreamState{nullptr, nullptr, 0},
                                  t % tiles_x, t / tiles_x, sm);
 }

@@ -161,7 +161,7 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
     double* __restrict__ part_theta, double* __restrict__ part_mo, float* __restrict__ part_rh) {
   __shared__ BwdSmem sm;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int tile = xcd_tile(blockIdx.x, bc.n_tiles);
+  const int tile = xcd_tile_runs<8>(blockIdx.x, bc.n_tiles);
   const int tile_x = tile % bc.tiles_x, tile_y = tile / bc.tiles_x;
   const int C0 = tile_x * MW, R0 = tile_y * BMH;
   const int ncol = min(MW, g.OW - C0), nrow = min(BMH, g.OH - R0);
