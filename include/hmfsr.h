@@ -168,7 +168,7 @@ typedef struct {
  *          float64 planes [3][out_height][out_width] with C per channel in raw
  *          units, then three float32 planes with the denominator (scaled by
  *          2^-m) and three with the reference exponent m (log2 units). With
- *          saved the normaliser is accumulated in float64 and the 64 x 16
+ *          saved the normaliser is accumulated in float64 and the default
  *          tile shape is used, so `out` can differ from a call without it in
  *          the last bits.
  * The internal workspace holds per-frame maps of the base half-resolution
@@ -409,8 +409,8 @@ hmfsr_status hmfsr_merge_batch(int32_t n_bursts, const hmfsr_desc* descs,
  * the workgroups each launch starts. Merge launch c (0..7) takes the bursts
  * of tile shape c / 2 (indices as for hmfsr_autotune) whose raw footprint is
  * loaded in batches of four (c even) or eight (c odd) samples per thread, as
- * the burst's own hmfsr_merge launch would. A workgroup pulls items until the list is exhausted, so
- * items / workgroups is how many it takes in turn. By default a launch starts
+ * the burst's own hmfsr_merge launch would. A workgroup pulls items until the
+ * list is exhausted, so items / workgroups is how many it takes in turn. By default a launch starts
  * min(items, compute units x resident workgroups per unit) workgroups;
  * HMFSR_BATCH_GROUPS=<k> (k >= 1) caps every launch at k when a graph is
  * captured (the cap is part of the graph's signature).
@@ -450,7 +450,7 @@ enum {
   HMFSR_STAGE_BATCH = 3,  /* one replay of a batched-merge graph       */
   HMFSR_STAGE_MERGE_BWD = 4,   /* adjoint of the accumulation              */
   HMFSR_STAGE_ROBUST_BWD = 5,  /* adjoint of the robustness                */
-  HMFSR_STAGE_GRAD_REDUCE = 6, /* fixed-order sums of the gradient partials */
+  HMFSR_STAGE_GRAD_REDUCE = 6, /* fixed-order sums of the tuning gradient */
   HMFSR_STAGE_ALIGN = 7,       /* tile alignment (pyramid, matching, Lucas-Kanade) */
   HMFSR_NUM_STAGES = 8
 };
