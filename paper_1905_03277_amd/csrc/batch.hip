@@ -348,6 +348,7 @@ hmfsr_status hmfsr_merge_batch(int32_t n_bursts, const hmfsr_desc* descs, const 
       hipStreamCaptureStatus cap_status = hipStreamCaptureStatusNone;
       if (hipStreamIsCapturing(s, &cap_status) != hipSuccess || cap_status != hipStreamCaptureStatusNone)
         return HMFSR_E_HIP;
+      P.ptrs.clear();  // until every block is written
       if (launch_set_buffers((BurstArgs*)(base + L.args), n_bursts, args.data(), s) != hipSuccess) return HMFSR_E_HIP;
       P.ptrs = ptrs;
     }
