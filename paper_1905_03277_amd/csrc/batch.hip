@@ -19,6 +19,7 @@
 
 #include "device_util.h"
 #include "host.h"
+#include "merge_common.h"
 
 namespace hmfsr {
 namespace {
@@ -448,8 +449,10 @@ hmfsr_status hmfsr_merge_batch(int32_t n_bursts, const hmfsr_desc* descs, const 
   for (int c = 0; c < kNumMergeClasses && err == hipSuccess; ++c) {
     const int cnt = group_start[c + 1] - group_start[c];
     if (cnt == 0) continue;
-    const int groups = capped(cnt, (size_t)cus * merge_batch_blocks_per_cu(c), cap);
-    err = launch_merge_batch(c, d_args, d_mitems + group_start[c], d_bounds + (1 + c) * (XCDS + 1),
+    bool exact = false;
+    for (int i = 0; i < n_bursts; ++i) exact = exact || (mcls[i] == c && exact_weights(geo[i].scale));
+    const int groups = capped(cnt, (size_t)cus * merge_batch_blocks_per_cu(c, exact), cap);
+    err = launch_merge_batch(c, exact, d_args, d_mitems + group_start[c], d_bounds + (1 + c) * (XCDS + 1),
                              d_counters + (1 + c) * XCDS, groups, cs);
     info.merge_items[c] = cnt;
     info.merge_groups[c] = groups;

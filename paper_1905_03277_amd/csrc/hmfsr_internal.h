@@ -118,9 +118,10 @@ hipError_t launch_merge(int variant, const Geometry& g, const MergeConsts& mc, c
 // raw-footprint loads go in batches of eight (the burst's own launch's choice).
 constexpr int kNumMergeClasses = 8;
 int merge_class(int variant, double scale);
-// `bounds` [XCDS + 1] and `counters` [XCDS] of the launch's item queue (see
+// exact: some burst of the launch takes exact R_hat weights. `bounds`
+// [XCDS + 1] and `counters` [XCDS] of the launch's item queue (see
 // for_each_item).
-hipError_t launch_merge_batch(int cls, const BurstArgs* bursts, const WorkItem* items, const int* bounds,
+hipError_t launch_merge_batch(int cls, bool exact, const BurstArgs* bursts, const WorkItem* items, const int* bounds,
                               int* counters, int n_groups, hipStream_t stream);
 hipError_t launch_robust_batch(const BurstArgs* bursts, const WorkItem* items, const int* bounds,
                                int* counters, int n_groups, hipStream_t stream);
@@ -144,7 +145,7 @@ hipError_t launch_merge_stream(const Geometry& g, const MergeConsts& mc, const u
                                int first, hipStream_t stream);
 hipError_t launch_stream_finish(const Geometry& g, const MergeConsts& mc, const float* state, float* out,
                                 hipStream_t stream);
-int merge_batch_blocks_per_cu(int cls);
+int merge_batch_blocks_per_cu(int cls, bool exact);
 int robust_batch_blocks_per_cu();
 int robust_tiles_x(const Geometry& g);
 int robust_tiles_y(const Geometry& g);

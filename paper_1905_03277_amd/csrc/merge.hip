@@ -6,40 +6,42 @@
 namespace hmfsr {
 namespace {
 
-template <int MH, int THREADS, int RB>
+template <int MH, int THREADS, int RB, bool EXACT>
 __global__ __launch_bounds__(THREADS, (waves_per_simd<MH, THREADS>())) void k_merge(
     const uint16_t* __restrict__ frames, const float* __restrict__ motion,
     const float* __restrict__ rmin, Geometry g, MergeConsts mc, float* __restrict__ out) {
-  __shared__ MergeSmem<MH> sm;
+  __shared__ MergeSmem<MH, EXACT> sm;
   const int tiles_x = (g.OW + MW - 1) / MW, n = tiles_x * ((g.OH + MH - 1) / MH);
   const int t = xcd_tile_runs<8>(blockIdx.x, n);
-  merge_tile<MH, THREADS, TILE_PLAIN, RB>(frames, motion, rmin, g, mc, out, nullptr, StreamState{nullptr, nullptr, 0},
-                                      t % tiles_x, t / tiles_x, sm);
+  merge_tile<MH, THREADS, TILE_PLAIN, RB, EXACT>(frames, motion, rmin, g, mc, out, nullptr,
+                                                 StreamState{nullptr, nullptr, 0}, t % tiles_x, t / tiles_x, sm);
 }
 
-// Forward that also keeps the normaliser for the adjoint (float64 accumulation).
-template <int MH, int RB>
-__global__ __launch_bounds__(256, 2) void k_merge_save(
+// Forward that also keeps the normaliser for the adjoint (float64
+// accumulation). Three waves per SIMD, 168 VGPRs; with EXACT, whose second
+// weight would take two more, by the launch bound.
+template <int MH, int RB, bool EXACT>
+__global__ __launch_bounds__(256, EXACT ? 3 : 2) void k_merge_save(
     const uint16_t* __restrict__ frames, const float* __restrict__ motion,
     const float* __restrict__ rmin, Geometry g, MergeConsts mc, float* __restrict__ out,
     float* __restrict__ saved) {
-  __shared__ MergeSmem<MH> sm;
+  __shared__ MergeSmem<MH, EXACT> sm;
   const int tiles_x = (g.OW + MW - 1) / MW, n = tiles_x * ((g.OH + MH - 1) / MH);
   const int t = xcd_tile_runs<8>(blockIdx.x, n);
-  merge_tile<MH, 256, TILE_SAVE, RB>(frames, motion, rmin, g, mc, out, saved, StreamState{nullptr, nullptr, 0},
-                                 t % tiles_x, t / tiles_x, sm);
+  merge_tile<MH, 256, TILE_SAVE, RB, EXACT>(frames, motion, rmin, g, mc, out, saved, StreamState{nullptr, nullptr, 0},
+                                            t % tiles_x, t / tiles_x, sm);
 }
 
 // Streaming form: frames from loop index st.first on are added to the state.
-template <int MH, int RB>
+template <int MH, int RB, bool EXACT>
 __global__ __launch_bounds__(256, 4) void k_merge_stream(
     const uint16_t* __restrict__ frames, const float* __restrict__ motion,
     const float* __restrict__ rmin, Geometry g, MergeConsts mc, StreamState st) {
-  __shared__ MergeSmem<MH> sm;
+  __shared__ MergeSmem<MH, EXACT> sm;
   const int tiles_x = (g.OW + MW - 1) / MW, n = tiles_x * ((g.OH + MH - 1) / MH);
   const int t = xcd_tile(blockIdx.x, n);
-  merge_tile<MH, 256, TILE_STREAM, RB>(frames, motion, rmin, g, mc, nullptr, nullptr, st, t % tiles_x, t / tiles_x,
-                                   sm);
+  merge_tile<MH, 256, TILE_STREAM, RB, EXACT>(frames, motion, rmin, g, mc, nullptr, nullptr, st, t % tiles_x,
+                                              t / tiles_x, sm);
 }
 
 // eq. (1) on a streaming state: C = num / den per channel, mapped to [0, 1].
@@ -54,40 +56,48 @@ __global__ void k_stream_finish(const float* __restrict__ state, size_t plane, f
 
 dim3 tile_grid(const Geometry& g, int rows) { return dim3(((g.OW + MW - 1) / MW) * ((g.OH + rows - 1) / rows)); }
 
+// Calls launch(RB, EXACT), two compile-time constants, with the raw-load batch
+// size and the weights' form that a tile shape takes at the burst's scale.
+template <typename F>
+hipError_t with_form(const Geometry& g, int rows, int threads, F launch) {
+  using W = std::integral_constant<int, 8>;
+  using N = std::integral_constant<int, 4>;
+  const bool wide = wide_raw_window(rows, threads, g.scale);
+  if (exact_weights(g.scale)) {
+    if (wide) launch(W{}, std::true_type{});
+    else launch(N{}, std::true_type{});
+  } else {
+    if (wide) launch(W{}, std::false_type{});
+    else launch(N{}, std::false_type{});
+  }
+  return hipGetLastError();
+}
+
 template <int MH, int THREADS>
 hipError_t launch_variant(const Geometry& g, const MergeConsts& mc, const uint16_t* frames,
                           const float* motion, const float* rmin, float* out, hipStream_t stream) {
-  if (wide_raw_window(MH, THREADS, g.scale))
-    hipLaunchKernelGGL((k_merge<MH, THREADS, 8>), tile_grid(g, MH), dim3(THREADS), 0, stream, frames, motion, rmin, g,
-                       mc, out);
-  else
-    hipLaunchKernelGGL((k_merge<MH, THREADS, 4>), tile_grid(g, MH), dim3(THREADS), 0, stream, frames, motion, rmin, g,
-                       mc, out);
-  return hipGetLastError();
+  return with_form(g, MH, THREADS, [&](auto rb, auto exact) {
+    hipLaunchKernelGGL((k_merge<MH, THREADS, decltype(rb)::value, decltype(exact)::value>), tile_grid(g, MH),
+                       dim3(THREADS), 0, stream, frames, motion, rmin, g, mc, out);
+  });
 }
 
 template <int MH>
 hipError_t launch_save(const Geometry& g, const MergeConsts& mc, const uint16_t* frames, const float* motion,
                        const float* rmin, float* out, float* saved, hipStream_t stream) {
-  if (wide_raw_window(MH, 256, g.scale))
-    hipLaunchKernelGGL((k_merge_save<MH, 8>), tile_grid(g, MH), dim3(256), 0, stream, frames, motion, rmin, g, mc,
-                       out, saved);
-  else
-    hipLaunchKernelGGL((k_merge_save<MH, 4>), tile_grid(g, MH), dim3(256), 0, stream, frames, motion, rmin, g, mc,
-                       out, saved);
-  return hipGetLastError();
+  return with_form(g, MH, 256, [&](auto rb, auto exact) {
+    hipLaunchKernelGGL((k_merge_save<MH, decltype(rb)::value, decltype(exact)::value>), tile_grid(g, MH), dim3(256), 0,
+                       stream, frames, motion, rmin, g, mc, out, saved);
+  });
 }
 
 template <int MH>
 hipError_t launch_stream(const Geometry& g, const MergeConsts& mc, const uint16_t* frames, const float* motion,
                          const float* rmin, StreamState st, hipStream_t stream) {
-  if (wide_raw_window(MH, 256, g.scale))
-    hipLaunchKernelGGL((k_merge_stream<MH, 8>), tile_grid(g, MH), dim3(256), 0, stream, frames, motion, rmin, g, mc,
-                       st);
-  else
-    hipLaunchKernelGGL((k_merge_stream<MH, 4>), tile_grid(g, MH), dim3(256), 0, stream, frames, motion, rmin, g, mc,
-                       st);
-  return hipGetLastError();
+  return with_form(g, MH, 256, [&](auto rb, auto exact) {
+    hipLaunchKernelGGL((k_merge_stream<MH, decltype(rb)::value, decltype(exact)::value>), tile_grid(g, MH), dim3(256),
+                       0, stream, frames, motion, rmin, g, mc, st);
+  });
 }
 
 // Rows of the 64-column, 256-thread tile for an output: 16 where that fills

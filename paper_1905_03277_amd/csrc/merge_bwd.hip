@@ -57,6 +57,14 @@ constexpr int BNV = 2 * BCP::VT;                                        // displ
 constexpr int BQB = (BCP::LUMA + BTHREADS - 1) / BTHREADS;               // quads per thread
 constexpr int BRHT = (BCP::RH + BTHREADS - 1) / BTHREADS;                // R_hat entries per thread
 
+// R_hat window rows of a pixel row (offsets in the window) and their weights.
+template <bool EXACT>
+struct BwdRow {
+  int ya, yb;
+  CellWeights<EXACT> y;
+};
+
+template <bool EXACT>
 struct BwdSmem {
   // the windows first: their addresses then fit the instructions' offsets
   float2 sRaw[BCP::RAW / 2];
@@ -66,10 +74,9 @@ struct BwdSmem {
   double sX[MW], sY[BMH];
   int sTyRow[BMH], sTxCol[MW];
   int sRlo[BCP::TY], sRhi[BCP::TY], sClo[BCP::TX], sChi[BCP::TX];
-  RowInfo sRow[BMH];
+  BwdRow<EXACT> sRow[BMH];
   int sRya[BMH], sRyb[BMH];           // R_hat window rows of each pixel row
   int sRxa[MW], sRxb[MW];             // R_hat window columns of each pixel column
-  float sRfx[MW];
   int sIlo[BCP::RH_H], sIhi[BCP::RH_H];  // pixel rows touching each window row
   float2 sV[BNV];     // displacement per frame slot and alignment tile (slot * ntiles + tile)
   int sBox[FCH][8];  // footprint of the whole tile per frame slot: Bounds, upper ends negated
@@ -154,12 +161,13 @@ __device__ __forceinline__ double wave_sum(double v) {
 // colours from two parities as in the forward, and three barriers per frame
 // instead of six: 701 -> 609 us for 8 x 768 x 1024 at scale 2, 50 -> 32 us for
 // 4 x 188 x 252 at 1.25.
+template <bool EXACT>
 __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
     const uint16_t* __restrict__ frames, const float* __restrict__ motion,
     const float* __restrict__ rmin, const float* __restrict__ saved,
     const float* __restrict__ grad_out, Geometry g, MergeConsts mc, BwdConsts bc,
     double* __restrict__ part_theta, double* __restrict__ part_mo, float* __restrict__ part_rh) {
-  __shared__ BwdSmem sm;
+  __shared__ BwdSmem<EXACT> sm;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tile = xcd_tile_runs<8>(blockIdx.x, bc.n_tiles);
   const int tile_x = tile % bc.tiles_x, tile_y = tile / bc.tiles_x;
@@ -209,27 +217,26 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
     const double fhy = floor(hy);
     const int y0 = (int)fhy;
     const int ya = clampi(y0, 0, g.h - 1) - rhr0, yb = clampi(y0 + 1, 0, g.h - 1) - rhr0;
-    RowInfo ri;
+    BwdRow<EXACT> ri;
     ri.ya = ya * rhw;
     ri.yb = yb * rhw;
-    ri.fy = (float)(hy - fhy);
+    ri.y.set(hy - fhy);
     sm.sRow[r] = ri;
     sm.sRya[r] = ya;
     sm.sRyb[r] = yb;
   }
   int rxa, rxb;
-  float rfx;
+  CellWeights<EXACT> rx;
   {
     const double hx = X * 0.5 - 0.5;
     const double fhx = floor(hx);
     rxa = clampi((int)fhx, 0, g.w - 1) - rhc0;
     rxb = clampi((int)fhx + 1, 0, g.w - 1) - rhc0;
-    rfx = (float)(hx - fhx);
+    rx.set(hx - fhx);
   }
   if (tid < MW) {
     sm.sRxa[tid] = rxa;
     sm.sRxb[tid] = rxb;
-    sm.sRfx[tid] = rfx;
   }
   __syncthreads();
   // pixel rows whose R_hat corners include window row I: the corners are
@@ -321,8 +328,8 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
         const int I = q / rhw, J = q - I * rhw;
         float s = 0.f;
         for (int r = sm.sIlo[I]; r <= sm.sIhi[I]; ++r) {
-          const float fyr = sm.sRow[r].fy;
-          const float wgt = (sm.sRya[r] == I ? 1.f - fyr : 0.f) + (sm.sRyb[r] == I ? fyr : 0.f);
+          const CellWeights<EXACT> y = sm.sRow[r].y;
+          const float wgt = (sm.sRya[r] == I ? y.first() : 0.f) + (sm.sRyb[r] == I ? y.f : 0.f);
           s = fmaf(wgt, sm.sHa[r][J] + sm.sHb[r][J], s);
         }
         part_rh[((size_t)m * bc.n_tiles + tile) * kBwdRH + q] = s;
@@ -352,7 +359,7 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
     const int t = __builtin_amdgcn_readfirstlane(sm.sTyRow[r]) - tyA;
     typack |= (unsigned)(r < nrow ? t : 0) << (4 * p);
   }
-  const RowInfo* rowv = sm.sRow + (tid >> 6) * BPX;
+  const BwdRow<EXACT>* rowv = sm.sRow + (tid >> 6) * BPX;
   const double* yv = sm.sY + (tid >> 6) * BPX;
   const float* sRaw = (const float*)sm.sRaw;
 
@@ -536,10 +543,9 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
             if (!whole && (tyl != sty || txl != stx)) continue;
             float rho = 1.f;
             if (!is_ref) {
-              const RowInfo ri = rowv[p];
-              const float top = sm.sRh[ri.ya + rxa] + rfx * (sm.sRh[ri.ya + rxb] - sm.sRh[ri.ya + rxa]);
-              const float bot = sm.sRh[ri.yb + rxa] + rfx * (sm.sRh[ri.yb + rxb] - sm.sRh[ri.yb + rxa]);
-              rho = top + ri.fy * (bot - top);
+              const BwdRow<EXACT> ri = rowv[p];
+              rho = ri.y.lerp(rx.lerp(sm.sRh[ri.ya + rxa], sm.sRh[ri.ya + rxb]),
+                              rx.lerp(sm.sRh[ri.yb + rxa], sm.sRh[ri.yb + rxb]));
               if (!(rho > 0.f)) continue;
             }
             const float2 v = sm.sV[slot * ntiles + mul24(tyl, ntx) + txl];
@@ -706,8 +712,8 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
             sm.sHa[r][lane] = 0.f;
             sm.sHb[r][lane] = 0.f;
           }
-          const float ga = run_sum((1.f - rfx) * pgr[p], lane, run_a);
-          const float gb = run_sum(rfx * pgr[p], lane, run_b);
+          const float ga = run_sum(rx.first() * pgr[p], lane, run_a);
+          const float gb = run_sum(rx.f * pgr[p], lane, run_b);
           if (end_a) sm.sHa[r][rxa] = ga;
           if (end_b) sm.sHb[r][rxb] = gb;
         }
@@ -1190,8 +1196,8 @@ hipError_t launch_merge_bwd(const Geometry& g, const MergeConsts& mc, const BwdC
                             const float* saved, const float* grad_out, const BwdWork& w,
                             hipStream_t stream) {
   const dim3 grid(bc.n_tiles);
-  hipLaunchKernelGGL(k_merge_bwd, grid, dim3(BTHREADS), 0, stream, frames, motion, rmin, saved, grad_out,
-                     g, mc, bc, w.part_theta, w.part_mo, w.part_rh);
+  hipLaunchKernelGGL((exact_weights(g.scale) ? k_merge_bwd<true> : k_merge_bwd<false>), grid, dim3(BTHREADS), 0,
+                     stream, frames, motion, rmin, saved, grad_out, g, mc, bc, w.part_theta, w.part_mo, w.part_rh);
   return hipGetLastError();
 }
 

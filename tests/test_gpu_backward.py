@@ -12,7 +12,8 @@ import pytest
 import torch
 
 import oracle.adjoint as oa
-from parity_util import crop_case
+import oracle.merge as om
+from parity_util import assert_parity, crop_case
 from paper_1905_03277_amd import synth, torch_ops
 
 pytestmark = pytest.mark.gpu
@@ -207,3 +208,23 @@ def test_full_size_differentiation_workload_on_a_window(window):
     full = np.zeros_like(got_m)
     full[:, y0:y0 + mo.shape[1], x0:x0 + mo.shape[2]] = want_m
     check(got_m, full, "motion gradient")
+
+
+@pytest.mark.parametrize("scale", [3.7, 7.3])
+@pytest.mark.parametrize("seed", [35, 36, 41])
+def test_weights_next_to_rejected_cells(scale, seed):
+    """Scales whose rows and columns come within 1e-7 of a half-resolution
+    cell's centre, beside cells where a frame is rejected (R_hat 0): the other
+    cell's weight, 3e-8 to 2e-7, is then the frame's whole weight, and decides
+    the pixel where the frame's samples lie much closer than the base's. Output
+    and gradients follow the oracle there."""
+    f, m, d, t, g_out = grad_case(scale=scale, seed=seed, n=3, h=36, w=34, tile=8, cfa=2)
+    print("[case] weights", scale, seed, flush=True)
+    out = torch_ops.merge(torch.from_numpy(f.astype(np.int16)).to(DEV), torch.from_numpy(m).to(DEV), d, t)
+    torch.cuda.synchronize()
+    assert_parity(out.cpu().numpy(), om.merge(f, m, d, t), f"scale {scale} seed {seed}")
+    want_t, want_m = oa.merge_backward(f, m, d, t, g_out)
+    got_t, got_m = gpu_backward(f, m, d, t, g_out)
+    if scale <= 4.0:
+        check(got_t, want_t, "tuning gradient")
+        check(got_m, want_m, "motion gradient")

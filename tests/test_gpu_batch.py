@@ -192,3 +192,26 @@ def test_persistent_loop_full_size_members():
             print("[case] full-size batch window", b.desc.n_frames, oy, ox, flush=True)
             want_w = oracle_crop(f, m, b.desc, b.tuning, oy, ox, S, S)
             assert_parity(o[:, oy:oy + S, ox:ox + S].cpu().numpy(), want_w, f"batch member window ({oy},{ox})")
+
+
+@pytest.mark.parametrize("scales", [(1.3, 2.2), (1.0, 1.3, 2.0, 3.7, 1.5)])
+@pytest.mark.parametrize("cap", [0, 2])
+def test_scales_with_exact_weights_bitwise(scales, cap, monkeypatch):
+    """Batches whose scales take exact R_hat weights, alone and beside scales
+    that do not: a launch then holds both forms of the tile body."""
+    if cap:
+        monkeypatch.setenv("HMFSR_BATCH_GROUPS", str(cap))
+    bursts = [synth.make_burst(3 + i, 40 + 8 * i, 72, seed=5100 + i, scale=s, tile_size=16)
+              for i, s in enumerate(scales)]
+    args = as_args(bursts)
+    print("[case] exact weights", scales, cap, flush=True)
+    want = per_burst(args)
+    outs = torch_ops.merge_batch(args)
+    torch.cuda.synchronize()
+    for i, (o, w) in enumerate(zip(outs, want)):
+        np.testing.assert_array_equal(o.cpu().numpy(), w, err_msg=f"burst {i}")
+    f, m, d, t = args[0]
+    sm = torch_ops.StreamingMerge(f[0].contiguous(), d, t)
+    for k in range(1, d.n_frames):
+        sm.add(f[k].contiguous(), m[k].contiguous())
+    np.testing.assert_array_equal(sm.result().cpu().numpy(), want[0])
