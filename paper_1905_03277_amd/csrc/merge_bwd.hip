@@ -809,15 +809,17 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {
 //
 // One wave per (frame, alignment tile). A wave is a chain of dependent round
 // trips to memory with little arithmetic between them, so every dL/dR_hat
-// partial of a block's cells (up to nine a cell, one per output tile whose
-// window holds it) is loaded before the first is added, at addresses that are
-// valid also where the partial does not exist; the output tiles of its rows
+// partial of a block's cells (one per output tile whose window holds the cell:
+// at most NTR tile rows, see robust_bwd_rows, and two columns) is loaded
+// before the first is added, at addresses that are valid also where the
+// partial does not exist; the output tiles of its rows
 // and columns are found by 60 lanes at once, and only the cells that reach the
 // block are visited. 8 x 768 x 1024 at scale 2: 73 -> 55 us; 4 x 188 x 252 at
 // scale 1.25 with 8 px tiles: 15.8 -> 9 us. (The pixels' statistics loaded
 // before their gradient is known to be nonzero: 101 registers, +0.5 %.)
 // The tile's merge partials of dL/dv are added here as well, in tile order: a
 // launch of its own took 9-12 us for it.
+template <int NTR>
 __global__ __launch_bounds__(64, 5) void k_robust_bwd(const uint2* __restrict__ gmu,
                                                    const float* __restrict__ gref,
                                                    const float* __restrict__ motion,
@@ -849,7 +851,7 @@ __global__ __launch_bounds__(64, 5) void k_robust_bwd(const uint2* __restrict__ 
   // block: how many, and per tile where the cell's row (column) begins in
   // part_rh and the window's width
   __shared__ int sNr[RB + 4], sNc[RB + 4];
-  __shared__ int2 sTr[RB + 4][3];  // tile row's first element, row in the window
+  __shared__ int2 sTr[RB + 4][NTR];  // tile row's first element, row in the window
   __shared__ int2 sTc[RB + 4][3];  // tile's first element + column in the window, window width
   const size_t plane = (size_t)g.h * g.w;
   const float* R = rmap + (size_t)n * plane;
@@ -893,7 +895,7 @@ __global__ __launch_bounds__(64, 5) void k_robust_bwd(const uint2* __restrict__ 
       const int xa = clampi((int)fhx, 0, g.w - 1), xb = clampi((int)fhx + 1, 0, g.w - 1);
       const int ya = clampi((int)fhy, 0, g.h - 1), yb = clampi((int)fhy + 1, 0, g.h - 1);
       // lane 5 r + c of an axis: does candidate tile c of cell row (column) r hold it?
-      auto tiles = [&](int first, int n_half, int n_out, int edge, int n_axis, auto&& put) {
+      auto tiles = [&](int first, int n_half, int n_out, int edge, int n_axis, int most, auto&& put) {
         const int r = tid / 5, c = tid - 5 * r, I = first + r;
         int lo = 0, hi = -1;
         const int t = (int)((2.0 * I + 1.0) * g.scale / edge) - 2 + c;
@@ -902,13 +904,13 @@ __global__ __launch_bounds__(64, 5) void k_robust_bwd(const uint2* __restrict__ 
         const bool in = I >= lo && I <= hi;
         const unsigned m = (unsigned)(__ballot(in) >> (5 * r)) & 31u;
         const int pos = __popc(m & ((1u << c) - 1u));
-        if (tid < 5 * (RB + 4)) put(r, c, min(__popc(m), 3), in && pos < 3 ? pos : -1, t, I - lo, hi - lo + 1);
+        if (tid < 5 * (RB + 4)) put(r, c, min(__popc(m), most), in && pos < most ? pos : -1, t, I - lo, hi - lo + 1);
       };
-      tiles(bi0 - 2, g.h, g.OH, BMH, bc.tiles_y, [&](int r, int c, int cnt, int pos, int t, int d, int) {
+      tiles(bi0 - 2, g.h, g.OH, BMH, bc.tiles_y, NTR, [&](int r, int c, int cnt, int pos, int t, int d, int) {
         if (c == 0) sNr[r] = cnt;
         if (pos >= 0) sTr[r][pos] = make_int2(t, d);
       });
-      tiles(bj0 - 2, g.w, g.OW, MW, bc.tiles_x, [&](int r, int c, int cnt, int pos, int t, int d, int wd) {
+      tiles(bj0 - 2, g.w, g.OW, MW, bc.tiles_x, 3, [&](int r, int c, int cnt, int pos, int t, int d, int wd) {
         if (c == 0) sNc[r] = cnt;
         if (pos >= 0) sTc[r][pos] = make_int2(t * kBwdRH + d, wd);
       });
@@ -925,9 +927,9 @@ __global__ __launch_bounds__(64, 5) void k_robust_bwd(const uint2* __restrict__ 
         const int k = min(tid + 64 * q, nr * nc - 1);
         const int r2 = split_row(k, ninv), c2 = k - r2 * nc;
         const int na = sNr[r2], nb = sNc[c2];
-        float v[3][3];
+        float v[NTR][3];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
+        for (int a = 0; a < NTR; ++a) {
           const int2 tr = sTr[r2][a];
           const float* row = part_rh + ((size_t)n * bc.n_tiles + (a < na ? tr.x * bc.tiles_x : 0)) * kBwdRH;
 #pragma unroll
@@ -938,7 +940,7 @@ __global__ __launch_bounds__(64, 5) void k_robust_bwd(const uint2* __restrict__ 
         }
         float gr = 0.f;
 #pragma unroll
-        for (int a = 0; a < 3; ++a)
+        for (int a = 0; a < NTR; ++a)
 #pragma unroll
           for (int b = 0; b < 3; ++b)
             if (a < na && b < nb) gr += v[a][b];
@@ -1146,6 +1148,17 @@ __global__ __launch_bounds__(256) void k_grad_tuning(const double* __restrict__ 
 
 size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
+// Most output tile rows whose R_hat windows hold one cell. A cell is a corner
+// of the output rows within one cell of it on either side, at most 4 scale
+// consecutive rows; 16 of them (scale 4) touch at most three tiles of eight
+// rows, 32 (scale 8, the largest accepted) at most five, among the five
+// candidates around the cell's own tile. (Columns: 32 of them touch at most
+// two tiles of 64.)
+int robust_bwd_rows(double scale) {
+  static_assert(BMH == 8 && MW == 64, "counted for tiles of 8 rows and 64 columns");
+  return scale <= 4.0 ? 3 : 5;
+}
+
 }  // namespace
 
 size_t bwd_bytes(const Geometry& g, bool need_saved) {
@@ -1205,8 +1218,12 @@ hipError_t launch_robust_bwd(const Geometry& g, const RobustConsts& rc, const Pr
                              const BwdConsts& bc, const float* motion, const BwdWork& w, float* grad_motion,
                              hipStream_t stream) {
   const dim3 grid(g.TX, g.TY, g.n);
-  hipLaunchKernelGGL(k_robust_bwd, grid, dim3(64), 0, stream, w.fwd.gmu, w.fwd.gref, motion, w.fwd.mov, w.rmap,
-                     w.part_rh, w.part_mo, g, rc, pc, bc, w.part_rob, grad_motion, w.ticket);
+  if (robust_bwd_rows(g.scale) == 3)
+    hipLaunchKernelGGL(k_robust_bwd<3>, grid, dim3(64), 0, stream, w.fwd.gmu, w.fwd.gref, motion, w.fwd.mov, w.rmap,
+                       w.part_rh, w.part_mo, g, rc, pc, bc, w.part_rob, grad_motion, w.ticket);
+  else
+    hipLaunchKernelGGL(k_robust_bwd<5>, grid, dim3(64), 0, stream, w.fwd.gmu, w.fwd.gref, motion, w.fwd.mov, w.rmap,
+                       w.part_rh, w.part_mo, g, rc, pc, bc, w.part_rob, grad_motion, w.ticket);
   return hipGetLastError();
 }
 

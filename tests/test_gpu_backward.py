@@ -225,6 +225,5 @@ def test_weights_next_to_rejected_cells(scale, seed):
     assert_parity(out.cpu().numpy(), om.merge(f, m, d, t), f"scale {scale} seed {seed}")
     want_t, want_m = oa.merge_backward(f, m, d, t, g_out)
     got_t, got_m = gpu_backward(f, m, d, t, g_out)
-    if scale <= 4.0:
-        check(got_t, want_t, "tuning gradient")
-        check(got_m, want_m, "motion gradient")
+    check(got_t, want_t, "tuning gradient")
+    check(got_m, want_m, "motion gradient")

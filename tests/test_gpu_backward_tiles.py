@@ -33,3 +33,23 @@ def test_tile_sums_match_oracle_adjoint(case):
     check(got_m, want_m, "motion gradient")
     assert np.all(got_m[d.ref_frame] == 0.0)
     torch.cuda.synchronize()
+
+
+# A cell of R_hat is read by 4 * scale output rows, which lie in up to three of
+# the adjoint's tiles of eight rows at scale 4 and up to five at scale 8.
+HIGH_SCALES = [dict(scale=4.0, seed=31, n=2, h=34, w=40, tile=8),
+               dict(scale=4.5, seed=32, n=3, h=34, w=40, tile=16, ref=1),
+               dict(scale=5.0, seed=33, n=2, h=40, w=34, tile=8, cfa=1),
+               dict(scale=6.7, seed=34, n=2, h=34, w=40, tile=16),
+               dict(scale=7.3, seed=35, n=3, h=36, w=34, tile=8, cfa=2),
+               dict(scale=8.0, seed=36, n=2, h=34, w=36, tile=32, ref=1)]
+
+
+@pytest.mark.parametrize("case", HIGH_SCALES, ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items()))
+def test_cells_of_many_output_tiles(case):
+    print("[case] high scale", case, flush=True)
+    f, m, d, t, g_out = grad_case(**case)
+    want_t, want_m = oa.merge_backward(f, m, d, t, g_out)
+    got_t, got_m = gpu_backward(f, m, d, t, g_out)
+    check(got_t, want_t, "tuning gradient")
+    check(got_m, want_m, "motion gradient")
