@@ -214,7 +214,7 @@ def bench_batch(dev, reps: int = 3) -> dict:
     """The uneven batched workload (64 bursts, 2-15 frames, 0.2-12 MP, scale
     1/1.5/2): one replay of the captured persistent-kernel graph versus one
     hmfsr_merge launch sequence per burst, after autotuning one burst of every
-    (scale, frame-count) class present."""
+    (output size, scale, frame-count) class present."""
     import torch
     from paper_1905_03277_amd import synth, torch_ops
 
@@ -225,7 +225,9 @@ def bench_batch(dev, reps: int = 3) -> dict:
             for b in bursts]
     tuned = {}
     for (f, m, d, t), o in zip(args, outs):
+        tiles = -(-d.out_width // 64) * -(-d.out_height // 16)
         key = (0 if d.scale <= 1 else 1 if d.scale <= 1.5 else 2,
+               2 if tiles <= 192 else 1 if tiles <= 384 else 0,
                0 if d.n_frames <= 4 else 1 if d.n_frames <= 8 else 2)
         if key not in tuned:
             tuned[key] = torch_ops.autotune(f, m, d, t, out=o)[0]
@@ -265,7 +267,7 @@ def bench_batch(dev, reps: int = 3) -> dict:
             "speedup": round(ms_loop / ms_graph, 3),
             "per_burst_MPs_loop": {"min": round(rates[0], 1), "median": round(rates[len(rates) // 2], 1),
                                    "max": round(rates[-1], 1)},
-            "tuned_shapes": {f"{k[0]}/{k[1]}": v for k, v in tuned.items()}}
+            "tuned_shapes": {"/".join(map(str, k)): v for k, v in tuned.items()}}
 
 
 def bench_config(cfg: int, dev, reps: int = 10) -> dict:

@@ -184,7 +184,7 @@ hmfsr_status hmfsr_merge(const hmfsr_desc* desc, const hmfsr_tuning* tuning,
  * hmfsr_merge_noalloc -- hmfsr_merge for callers that cannot allocate device
  * memory: code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc. Same arguments, kernels and results as hmfsr_merge (bit
- * for bit, for the same tile shape), but the per-frame maps live in a
+ * for bit), but the per-frame maps live in a
  * static scratch array of HMFSR_NOALLOC_SCRATCH_BYTES per device, which the
  * library's code object holds from load until the process ends; the call
  * allocates nothing (no hipMalloc, hipFree, events or library allocations)
@@ -238,7 +238,7 @@ hmfsr_status hmfsr_merge_backward(const hmfsr_desc* desc, const hmfsr_tuning* tu
  * Streaming merge -- frames added one call at a time into a caller-owned
  * accumulator state, so that memory does not grow with the frame count (the
  * paper's online merge, Sec. 5.1 and 6.5). The result equals hmfsr_merge's
- * with the 64 x 16 tile shape bit for bit when the frames are added in the
+ * bit for bit when the frames are added in the
  * order hmfsr_merge visits them (base frame, then the others in index order).
  *  state  DEVICE float32 [9][out_height][out_width], caller-owned: per
  *         channel the numerator and denominator of eq. (1) (raw units, scaled
@@ -395,8 +395,7 @@ hmfsr_status hmfsr_merge_maps(const hmfsr_desc* desc, const hmfsr_tuning* tuning
  * instantiates the graph (synchronising `stream` once); later calls with the
  * same descriptors replay it, writing changed buffer addresses (in stream
  * order) and uploading changed tuning values (after synchronising `stream`)
- * first. Results equal hmfsr_merge's
- * for the same tile shape bit for bit.
+ * first. Results equal hmfsr_merge's bit for bit.
  */
 hmfsr_status hmfsr_merge_batch(int32_t n_bursts, const hmfsr_desc* descs,
                                const hmfsr_tuning* tunings, const uint16_t* const* frames,
@@ -407,9 +406,9 @@ hmfsr_status hmfsr_merge_batch(int32_t n_bursts, const hmfsr_desc* descs,
  * current device (host values, no device work): the (burst, tile) items of
  * the persistent robustness launch and of each persistent merge launch, and
  * the workgroups each launch starts. Merge launch c (0..7) takes the bursts
- * of tile shape c / 2 (indices as for hmfsr_autotune) whose raw footprint is
- * loaded in batches of four (c even) or eight (c odd) samples per thread, as
- * the burst's own hmfsr_merge launch would. A workgroup pulls items until the
+ * of tile shape c / 2 (indices as for hmfsr_autotune, small outputs too) whose
+ * raw footprint is loaded in batches of four (c even) or eight (c odd) samples
+ * per thread. A workgroup pulls items until the
  * list is exhausted, so items / workgroups is how many it takes in turn. By default a launch starts
  * min(items, compute units x resident workgroups per unit) workgroups;
  * HMFSR_BATCH_GROUPS=<k> (k >= 1) caps every launch at k when a graph is
@@ -423,13 +422,19 @@ typedef struct {
 hmfsr_status hmfsr_batch_plan(hmfsr_batch_info* out);
 
 /*
- * hmfsr_autotune -- time every compiled tile shape of the merge kernel on this
- * burst (synchronising `stream`), remember the fastest for the burst's class
- * (output scale <= 1, <= 1.5, <= 2, > 2 x frame count <= 4, <= 8, <= 15, > 15)
- * and use it for later merges of that class. With HMFSR_TUNE_CACHE=<file> the
- * table is read at first use and rewritten after each tuning. `out` receives
- * the merge; `chosen` (host, nullable) the index of the chosen shape.
- * HMFSR_MERGE_VARIANT=<index> overrides every choice.
+ * hmfsr_autotune -- time the tile shapes of the merge kernel on this burst
+ * (synchronising `stream`), remember the fastest for the burst's class and use
+ * it for later merges of that class. Shapes, by index: 0 64 x 32 pixels with
+ * 256 threads, 1 64 x 32 with 512, 2 (the default) 64 x 16 with 256, 3 64 x 16
+ * with 128. On small outputs, of up to 384 (192) tiles of 64 x 16, the default
+ * is 64 x 8 (64 x 4) with 256 threads, also for index 2 here, except in
+ * hmfsr_merge_batch. Classes: output of > 384, <= 384, <= 192 tiles x scale <=
+ * 1, <= 1.5, <= 2, > 2 x frame count <= 4, <= 8, <= 15, > 15. With
+ * HMFSR_TUNE_CACHE=<file> the table is read at first use and rewritten after
+ * each tuning. `out` receives the merge; `chosen` (host, nullable) the index
+ * of the chosen shape. HMFSR_MERGE_VARIANT=<index> overrides every choice with
+ * exactly that shape (merges that keep a normaliser and streamed merges always
+ * take the default). All shapes give the same bits.
  */
 hmfsr_status hmfsr_autotune(const hmfsr_desc* desc, const hmfsr_tuning* tuning,
                             const uint16_t* frames, const float* motion, float* out, void* stream,

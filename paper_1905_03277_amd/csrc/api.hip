@@ -278,13 +278,13 @@ hipError_t run_robust(const Geometry& g, const RobustConsts& rc, const PriorCons
 
 hmfsr_status run_merge(const hmfsr_desc* desc, const hmfsr_tuning* tuning, const Geometry& g,
                        const uint16_t* frames, const float* motion, float* out, float* saved,
-                       const Work& w, int variant, hipStream_t s, bool profiled) {
+                       const Work& w, int shape, hipStream_t s, bool profiled) {
   const PriorConsts pc = make_prior(tuning);
   const RobustConsts rc = make_robust(desc, tuning);
   const MergeConsts mc = make_merge(desc, tuning, g);
   auto run = [&](int stage, auto fn) { return profiled ? timed(stage, s, fn) : fn(); };
   if (run_robust(g, rc, pc, frames, motion, w, w.rmin, nullptr, s, profiled) != hipSuccess) return HMFSR_E_HIP;
-  if (run(HMFSR_STAGE_MERGE, [&] { return launch_merge(variant, g, mc, frames, motion, w.rmin, out, saved, s); }) !=
+  if (run(HMFSR_STAGE_MERGE, [&] { return launch_merge(shape, g, mc, frames, motion, w.rmin, out, saved, s); }) !=
       hipSuccess)
     return HMFSR_E_HIP;
   return HMFSR_OK;
@@ -311,7 +311,7 @@ hmfsr_status hmfsr_merge(const hmfsr_desc* desc, const hmfsr_tuning* tuning, con
   hipStream_t s = (hipStream_t)stream;
   if (debug_enabled() && (st = debug_check_motion(dev, motion, g.n, g.ref, g.TY, g.TX, s)) != HMFSR_OK) return st;
   if ((st = workspace(dev, work_bytes(g), s, &ws)) != HMFSR_OK) return st;
-  return run_merge(desc, tuning, g, frames, motion, out, saved, work_carve(ws, g), merge_variant(g), s);
+  return run_merge(desc, tuning, g, frames, motion, out, saved, work_carve(ws, g), merge_shape(g), s);
 }
 
 hmfsr_status hmfsr_stream_begin(const hmfsr_desc* desc, const hmfsr_tuning* tuning, const uint16_t* base_frame,
@@ -423,7 +423,7 @@ hmfsr_status hmfsr_merge_backward(const hmfsr_desc* desc, const hmfsr_tuning* tu
   if (run_robust(g, rc, pc, frames, motion, w.fwd, w.fwd.rmin, w.rmap, s, true) != hipSuccess) return HMFSR_E_HIP;
   if (need_saved) {
     if (timed(HMFSR_STAGE_MERGE, s, [&] {
-          return launch_merge(merge_variant(g), g, mc, frames, motion, w.fwd.rmin, nullptr, w.saved, s);
+          return launch_merge(merge_shape(g), g, mc, frames, motion, w.fwd.rmin, nullptr, w.saved, s);
         }) != hipSuccess)
       return HMFSR_E_HIP;
     saved = w.saved;

@@ -20,29 +20,33 @@
 #include "device_util.h"
 #include "host.h"
 #include "merge_common.h"
+#include "merge_shape.h"
 
 namespace hmfsr {
 namespace {
 
-constexpr int kDefaultVariant = 2;  // 64x16 tile, 256 threads
-
 // ---- autotuner --------------------------------------------------------------
-// The best tile shape depends mostly on the output scale (footprint per output
-// pixel) and on the frame count (how long accumulators live per workgroup).
+// The best tile shape depends mostly on the output's size (size_class: the
+// tiles there are to fill the device), the output scale (footprint per output
+// pixel) and the frame count (how long accumulators live per workgroup). A row
+// of the table is a size and a scale, 4 x size_class + scale_class, so that
+// the lines of large outputs are the same as in a table without sizes.
+constexpr int kTuneRows = 4 * kSizeClasses;
 struct TuneTable {
-  int v[4][4];
-  bool tuned[4][4];
+  int v[kTuneRows][4];
+  bool tuned[kTuneRows][4];
   bool loaded = false;
 };
 TuneTable g_tune;
 
 int scale_class(double s) { return s <= 1.0 ? 0 : (s <= 1.5 ? 1 : (s <= 2.0 ? 2 : 3)); }
 int frame_bucket(int n) { return n <= 4 ? 0 : (n <= 8 ? 1 : (n <= 15 ? 2 : 3)); }
+int tune_row(const Geometry& g) { return 4 * size_class(tiles_64x16(g.OH, g.OW)) + scale_class(g.scale); }
 
 void tune_load() {
   if (g_tune.loaded) return;
   g_tune.loaded = true;
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < kTuneRows; ++a)
     for (int b = 0; b < 4; ++b) {
       g_tune.v[a][b] = kDefaultVariant;
       g_tune.tuned[a][b] = false;
@@ -53,7 +57,7 @@ void tune_load() {
   if (!f) return;
   int a, b, v;
   while (fscanf(f, "%d %d %d", &a, &b, &v) == 3) {
-    if (a >= 0 && a < 4 && b >= 0 && b < 4 && v >= 0 && v < kNumMergeVariants) {
+    if (a >= 0 && a < kTuneRows && b >= 0 && b < 4 && v >= 0 && v < kNumMergeVariants) {
       g_tune.v[a][b] = v;
       g_tune.tuned[a][b] = true;
     }
@@ -66,7 +70,7 @@ void tune_save() {
   if (!path) return;
   FILE* f = fopen(path, "w");
   if (!f) return;
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < kTuneRows; ++a)
     for (int b = 0; b < 4; ++b)
       if (g_tune.tuned[a][b]) fprintf(f, "%d %d %d\n", a, b, g_tune.v[a][b]);
   fclose(f);
@@ -156,14 +160,24 @@ hipError_t launch_set_buffers(BurstArgs* bursts, int n_bursts, const BurstArgs* 
   return hipSuccess;
 }
 
-int merge_variant(const Geometry& g) {
+namespace {
+// HMFSR_MERGE_VARIANT, or -1.
+int forced_variant() {
   const char* env = getenv("HMFSR_MERGE_VARIANT");
-  if (env) {
-    const int v = atoi(env);
-    if (v >= 0 && v < kNumMergeVariants) return v;
-  }
+  const int v = env ? atoi(env) : -1;
+  return v >= 0 && v < kNumMergeVariants ? v : -1;
+}
+}  // namespace
+
+int merge_variant(const Geometry& g) {
+  const int forced = forced_variant();
+  if (forced >= 0) return forced;
   tune_load();
-  return g_tune.v[scale_class(g.scale)][frame_bucket(g.n)];
+  return g_tune.v[tune_row(g)][frame_bucket(g.n)];
+}
+
+int merge_shape(const Geometry& g) {
+  return burst_shape(forced_variant(), merge_variant(g), tiles_64x16(g.OH, g.OW));
 }
 
 }  // namespace hmfsr
@@ -187,18 +201,21 @@ hmfsr_status hmfsr_autotune(const hmfsr_desc* desc, const hmfsr_tuning* tuning,
   hipStream_t s = (hipStream_t)stream;
   if ((st = workspace(dev, work_bytes(g), s, &ws)) != HMFSR_OK) return st;
   const Work w = work_carve(ws, g);
-  // robustness once, then every tile shape: one warm-up and three timed launches
-  if ((st = run_merge(desc, tuning, g, frames, motion, out, nullptr, w, kDefaultVariant, s)) != HMFSR_OK) return st;
+  // robustness once, then every tile shape (for the default index the shape
+  // that merges of this size then run): one warm-up and three timed launches
+  const int tiles = tiles_64x16(g.OH, g.OW);
+  if ((st = run_merge(desc, tuning, g, frames, motion, out, nullptr, w, default_shape(tiles), s)) != HMFSR_OK) return st;
   const MergeConsts mc = make_merge(desc, tuning, g);
   hipEvent_t a = nullptr, b = nullptr;
   if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&b) != hipSuccess) return HMFSR_E_HIP;
   int best = kDefaultVariant;
   float best_ms = 1e30f;
   for (int v = 0; v < kNumMergeVariants && st == HMFSR_OK; ++v) {
-    if (launch_merge(v, g, mc, frames, motion, w.rmin, out, nullptr, s) != hipSuccess) st = HMFSR_E_HIP;
+    const int shape = burst_shape(-1, v, tiles);
+    if (launch_merge(shape, g, mc, frames, motion, w.rmin, out, nullptr, s) != hipSuccess) st = HMFSR_E_HIP;
     if (hipEventRecord(a, s) != hipSuccess) st = HMFSR_E_HIP;
     for (int r = 0; r < 3 && st == HMFSR_OK; ++r)
-      if (launch_merge(v, g, mc, frames, motion, w.rmin, out, nullptr, s) != hipSuccess) st = HMFSR_E_HIP;
+      if (launch_merge(shape, g, mc, frames, motion, w.rmin, out, nullptr, s) != hipSuccess) st = HMFSR_E_HIP;
     float ms = 0.f;
     if (hipEventRecord(b, s) != hipSuccess || hipEventSynchronize(b) != hipSuccess ||
         hipEventElapsedTime(&ms, a, b) != hipSuccess)
@@ -212,10 +229,11 @@ hmfsr_status hmfsr_autotune(const hmfsr_desc* desc, const hmfsr_tuning* tuning,
   (void)hipEventDestroy(b);
   if (st != HMFSR_OK) return st;
   // leave `out` holding the merge of the chosen shape
-  if (launch_merge(best, g, mc, frames, motion, w.rmin, out, nullptr, s) != hipSuccess) return HMFSR_E_HIP;
+  if (launch_merge(burst_shape(-1, best, tiles), g, mc, frames, motion, w.rmin, out, nullptr, s) != hipSuccess)
+    return HMFSR_E_HIP;
   tune_load();
-  g_tune.v[scale_class(g.scale)][frame_bucket(g.n)] = best;
-  g_tune.tuned[scale_class(g.scale)][frame_bucket(g.n)] = true;
+  g_tune.v[tune_row(g)][frame_bucket(g.n)] = best;
+  g_tune.tuned[tune_row(g)][frame_bucket(g.n)] = true;
   tune_save();
   if (chosen) *chosen = best;
   return HMFSR_OK;

@@ -107,11 +107,12 @@ struct MergeVariant {
 };
 extern const MergeVariant kMergeVariants[];
 extern const int kNumMergeVariants;
-// out and saved are each nullable. saved receives the normaliser of eq. (1),
-// accumulated in float64 (the default tile shape is then used): three float64
+// shape: an index of kMergeVariants or a smaller form of the default one
+// (merge_shape.h). out and saved are each nullable. saved receives the normaliser of eq. (1),
+// accumulated in float64 (the output's default shape is then used): three float64
 // planes C per channel (raw units), then three float32 planes of the
 // denominator and three of the reference exponent (12 4-byte words per pixel).
-hipError_t launch_merge(int variant, const Geometry& g, const MergeConsts& mc, const uint16_t* frames,
+hipError_t launch_merge(int shape, const Geometry& g, const MergeConsts& mc, const uint16_t* frames,
                         const float* motion, const float* rmin, float* out, float* saved,
                         hipStream_t stream);
 // Class of a burst in the batched merge: 2 x tile shape + 1 where the
@@ -137,7 +138,7 @@ hipError_t launch_set_buffers(BurstArgs* bursts, int n_bursts, const BurstArgs* 
 int base_stats_groups(const Geometry& g);
 int frame_means_groups(const Geometry& g);
 int merge_tile_rows(int variant);
-// Streaming merge (64 x 16 tiles): frames from loop index `first` on are added
+// Streaming merge (the output's default tile shape): frames from loop index `first` on are added
 // to the accumulator state [9][OH][OW] (numerator, denominator, reference
 // exponent per channel); state_in nullable (empty accumulators).
 hipError_t launch_merge_stream(const Geometry& g, const MergeConsts& mc, const uint16_t* frames,

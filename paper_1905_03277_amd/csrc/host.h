@@ -94,14 +94,17 @@ bool debug_enabled();
 // naming the first one) if any (caller holds g_mutex).
 hmfsr_status debug_check_motion(int dev, const float* motion, int n, int ref, int TY, int TX, hipStream_t s);
 
-// Merge tile shape for a burst: HMFSR_MERGE_VARIANT, else the autotuned
-// choice for the burst's (scale, frame count) class, else the default.
+// Merge tile shape for a burst of a batch: HMFSR_MERGE_VARIANT, else the
+// autotuned choice for the burst's (output size, scale, frame count) class,
+// else the default; and for a burst's own merge, whose default depends on the
+// output's size (merge_shape.h).
 int merge_variant(const Geometry& g);
+int merge_shape(const Geometry& g);
 // The three kernels of one merge on `s` (workspace from `workspace`). With
 // `profiled` false the launches are never bracketed by timing events (which
 // the event pool may have to create).
 hmfsr_status run_merge(const hmfsr_desc* desc, const hmfsr_tuning* tuning, const Geometry& g,
                        const uint16_t* frames, const float* motion, float* out, float* saved,
-                       const Work& w, int variant, hipStream_t s, bool profiled = true);
+                       const Work& w, int shape, hipStream_t s, bool profiled = true);
 
 }  // namespace hmfsr

@@ -1,6 +1,7 @@
 // Per-burst forward merge kernels (one launch over a burst's output tiles),
 // the normaliser-keeping forward of the adjoint and the streaming merge; the
 // tile body is merge_tile.h.
+#include "merge_shape.h"
 #include "merge_tile.h"
 
 namespace hmfsr {
@@ -100,19 +101,6 @@ hipError_t launch_stream(const Geometry& g, const MergeConsts& mc, const uint16_
   });
 }
 
-// Rows of the 64-column, 256-thread tile for an output: 16 where that fills
-// the 256 compute units, else fewer, so that more of them work and a frame's
-// chain (stage, Omega, one to four pixels a thread) is shorter. A pixel's
-// arithmetic does not depend on the shape: the results are the same bits.
-// Measured with 64 x 16 tiles / 64 x 8 / 64 x 4, us per merge: 8 x 256 x 256
-// (64 tiles of 64 x 16) 54.6 / 39.5 / 33.7, 8 x 384 x 512 (192) 57.5 / 48.5 /
-// 46.0, 8 x 256 x 256 at scale 2 (256) 51.1 / 44.9 / 47.0, 8 x 512 x 512 at
-// 1.5 (576) 75.9 / 75.3 / 82.6, 5 x 750 x 1002 at 1.5 (1704) 98 / 114 / 139.
-int small_tile_rows(const Geometry& g) {
-  const unsigned tiles = tile_grid(g, 16).x;
-  return tiles <= 192 ? 4 : (tiles <= 384 ? 8 : 16);
-}
-
 }  // namespace
 
 const MergeVariant kMergeVariants[] = {
@@ -120,22 +108,20 @@ const MergeVariant kMergeVariants[] = {
 };
 const int kNumMergeVariants = sizeof(kMergeVariants) / sizeof(kMergeVariants[0]);
 
-hipError_t launch_merge(int variant, const Geometry& g, const MergeConsts& mc, const uint16_t* frames,
+hipError_t launch_merge(int shape, const Geometry& g, const MergeConsts& mc, const uint16_t* frames,
                         const float* motion, const float* rmin, float* out, float* saved,
                         hipStream_t stream) {
-  const int rows = small_tile_rows(g);
-  if (saved) {  // 64 columns, 256 threads keep the normaliser
-    if (rows == 4) return launch_save<4>(g, mc, frames, motion, rmin, out, saved, stream);
-    if (rows == 8) return launch_save<8>(g, mc, frames, motion, rmin, out, saved, stream);
-    return launch_save<16>(g, mc, frames, motion, rmin, out, saved, stream);
-  }
-  switch (variant) {
+  if (saved) switch (default_shape(tiles_64x16(g.OH, g.OW))) {  // 64 columns, 256 threads keep the normaliser
+      case kShape64x4: return launch_save<4>(g, mc, frames, motion, rmin, out, saved, stream);
+      case kShape64x8: return launch_save<8>(g, mc, frames, motion, rmin, out, saved, stream);
+      default: return launch_save<16>(g, mc, frames, motion, rmin, out, saved, stream);
+    }
+  switch (shape) {
     case 1: return launch_variant<32, 512>(g, mc, frames, motion, rmin, out, stream);
-    case 2:
-      if (rows == 4) return launch_variant<4, 256>(g, mc, frames, motion, rmin, out, stream);
-      if (rows == 8) return launch_variant<8, 256>(g, mc, frames, motion, rmin, out, stream);
-      return launch_variant<16, 256>(g, mc, frames, motion, rmin, out, stream);
+    case 2: return launch_variant<16, 256>(g, mc, frames, motion, rmin, out, stream);
     case 3: return launch_variant<16, 128>(g, mc, frames, motion, rmin, out, stream);
+    case kShape64x8: return launch_variant<8, 256>(g, mc, frames, motion, rmin, out, stream);
+    case kShape64x4: return launch_variant<4, 256>(g, mc, frames, motion, rmin, out, stream);
     default: return launch_variant<32, 256>(g, mc, frames, motion, rmin, out, stream);
   }
 }
@@ -150,9 +136,9 @@ hipError_t launch_merge_stream(const Geometry& g, const MergeConsts& mc, const u
                                const float* motion, const float* rmin, const float* state_in, float* state_out,
                                int first, hipStream_t stream) {
   const StreamState st{state_in, state_out, first};
-  switch (small_tile_rows(g)) {
-    case 4: return launch_stream<4>(g, mc, frames, motion, rmin, st, stream);
-    case 8: return launch_stream<8>(g, mc, frames, motion, rmin, st, stream);
+  switch (default_shape(tiles_64x16(g.OH, g.OW))) {
+    case kShape64x4: return launch_stream<4>(g, mc, frames, motion, rmin, st, stream);
+    case kShape64x8: return launch_stream<8>(g, mc, frames, motion, rmin, st, stream);
     default: return launch_stream<16>(g, mc, frames, motion, rmin, st, stream);
   }
 }

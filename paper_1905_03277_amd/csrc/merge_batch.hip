@@ -7,9 +7,9 @@ namespace hmfsr {
 namespace {
 
 // Persistent form: workgroups pull (burst, tile) items from the XCD-chunked
-// queue (for_each_item) until it is exhausted. One launch per tile shape and
-// raw-load batch size (RB), so that every burst runs the code its own launch
-// would. EXACT: some burst of the launch takes exact R_hat weights; the kernel
+// queue (for_each_item) until it is exhausted. One launch per tile shape of
+// kMergeVariants and raw-load batch size (RB); small outputs take 64 x 16 here,
+// the batch's other tiles filling the device. EXACT: some burst of the launch takes exact R_hat weights; the kernel
 // then holds both forms of the tile body, and takes each item's. (Both forms in
 // every launch spill registers: twelve bursts 1531 -> 1570 us. A launch per
 // form ends in one more nearly empty round: three bursts at scales 1, 1.3 and

@@ -53,6 +53,6 @@ extern "C" hmfsr_status hmfsr_merge_noalloc(const hmfsr_desc* desc, const hmfsr_
   void* ws = nullptr;
   if ((st = scratch_of(dev, &ws)) != HMFSR_OK) return st;
   // every map the kernels read is written first in the same call: no clearing
-  return run_merge(desc, tuning, g, frames, motion, out, saved, work_carve(ws, g), merge_variant(g),
+  return run_merge(desc, tuning, g, frames, motion, out, saved, work_carve(ws, g), merge_shape(g),
                    (hipStream_t)stream, /*profiled=*/false);
 }

@@ -155,8 +155,7 @@ class StreamingMerge:
     """Frames added one at a time into a fixed-size accumulator state
     ([9][OH][OW] float32), then normalised: memory does not grow with the
     frame count. Adding the frames in the order ``merge`` visits them (base
-    frame first, then the others by index) reproduces ``merge`` with the
-    64 x 16 tile shape bit for bit."""
+    frame first, then the others by index) reproduces ``merge`` bit for bit."""
 
     def __init__(self, base_frame: torch.Tensor, desc, tuning):
         if not base_frame.is_cuda or base_frame.dtype not in (torch.uint16, torch.int16) \

@@ -215,3 +215,42 @@ def test_scales_with_exact_weights_bitwise(scales, cap, monkeypatch):
     for k in range(1, d.n_frames):
         sm.add(f[k].contiguous(), m[k].contiguous())
     np.testing.assert_array_equal(sm.result().cpu().numpy(), want[0])
+
+
+def test_tuning_a_small_output_leaves_large_ones_alone(monkeypatch, tmp_path):
+    """Tuned choices are kept per output size as well: lines of the table are 4
+    x size class + scale class, frame bucket, index."""
+    monkeypatch.setenv("HMFSR_TUNE_CACHE", str(tmp_path / "tune.txt"))
+
+    def lines():
+        return {tuple(map(int, ln.split()[:2])): int(ln.split()[2])
+                for ln in (tmp_path / "tune.txt").read_text().splitlines()}
+
+    # 40 frames: a bucket that no other test tunes
+    chosen = {}
+    for h, w, key in ((64, 384, (8, 3)), (512, 1024, (0, 3))):   # 24 and 512 tiles of 64 x 16 at scale 1
+        b = synth.make_burst(40, h, w, seed=78, scale=1.0, tile_size=16)
+        f, m = b.frames.to(DEV), b.motion.to(DEV)
+        print("[case] tune", h, w, flush=True)
+        chosen[key], out = torch_ops.autotune(f, m, b.desc, b.tuning)
+        want = torch_ops.merge(f, m, b.desc, b.tuning)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(out.cpu().numpy(), want.cpu().numpy())
+        assert {k: v for k, v in lines().items() if k[1] == 3} == chosen
+
+
+@pytest.mark.parametrize("scale,tile,spread", [(1.5, 16, 0.0), (2.0, 8, 40.0), (1.3, 32, 40.0), (3.0, 16, 0.0)])
+def test_every_shape_gives_the_same_bits(scale, tile, spread, monkeypatch):
+    b = synth.make_burst(5, 150, 202, seed=79, scale=scale, tile_size=tile)
+    m = b.motion.clone()
+    if spread:
+        m[1:] += torch.from_numpy(np.random.default_rng(80).uniform(-spread, spread, tuple(m[1:].shape)).astype(np.float32))
+    f, m = b.frames.to(DEV), m.to(DEV)
+    print("[case] shapes", scale, tile, spread, flush=True)
+    want = torch_ops.merge_batch([(f, m, b.desc, b.tuning)])[0].cpu().numpy()
+    for forced in (None, 0, 1, 2, 3):
+        if forced is not None:
+            monkeypatch.setenv("HMFSR_MERGE_VARIANT", str(forced))
+        got = torch_ops.merge(f, m, b.desc, b.tuning)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(got.cpu().numpy(), want, err_msg=f"shape {forced}")
