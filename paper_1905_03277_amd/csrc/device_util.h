@@ -43,11 +43,14 @@ __device__ __forceinline__ int xcd_tile(int b, int n) {
 // The same with several runs per XCD, the eight XCDs' runs interleaved: where
 // a tile's cost varies over the image (windows that do not fit, borders), no
 // XCD keeps the dear part for itself. A bijection on [0, n): the remainder of
-// n / (XCDS * RUNS) comes last, in order. The merge kernels take eight runs:
-// 12 MP x 8 0.977 -> 0.972 ms, 15 x 3 MP at scale 2 1.272 -> 1.261, 8 x 768 x
-// 1024 forward and adjoint 1.051 -> 1.044 (16 and 32 runs the same); the
-// streaming merge and the alignment lose 0.8 and 1 % with them, their
-// neighbours' data being worth more in one L2.
+// n / (XCDS * RUNS) comes last, in order. The merge kernels take eight runs,
+// measured against one in turn: 15 x 3 MP at scale 2 1271 -> 1258 us, 8 x 3 MP
+// with a divergent field 357 -> 352, the forward that keeps its normaliser at
+// 8 x 768 x 1024 275 -> 269 (scale 2) and 112 -> 109 (scale 1). At 12 MP x 8
+// they give 984 -> 982 (31 rounds), inside the spread of single runs, for 317
+// -> 353 MB read from HBM; the adjoint takes 671 us either way, 495 -> 492 and
+// 374 -> 380 on divergent fields. The streaming merge and the alignment lose
+// 0.8 and 1 % with them, their neighbours' data being worth more in one L2.
 template <int RUNS>
 __host__ __device__ __forceinline__ int xcd_tile_runs(int b, int n) {
   const int len = n / (XCDS * RUNS), x = b % XCDS, k = b / XCDS;

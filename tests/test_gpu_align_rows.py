@@ -10,6 +10,8 @@ result, float64 sums)."""
 import numpy as np
 import pytest
 
+import oracle.align as oa
+
 from paper_1905_03277_amd import synth
 from test_gpu_align import check_full
 
@@ -39,3 +41,48 @@ def test_rows_and_columns(n, h, w, tile, ref, params, extreme):
         f, _ = b.numpy()
         d = b.desc
     check_full(f, d.replace(ref_frame=ref), params, what=f"{n}x{h}x{w} t{tile} extreme={extreme}")
+
+
+def coherent_frames(h, w, seed):
+    """A base frame of 0 to 3 and a frame of 65535 less 0 to 3 (periodic over
+    eight) per 16 x 16 raw pixels, a level-3 pixel: every candidate of a level-3
+    block costs about 2^54, and the candidates differ by the correlation of the
+    small terms, a few units."""
+    rng = np.random.default_rng(seed)
+    ph, pw = -(-h // 16), -(-w // 16)
+    r = np.tile(rng.integers(0, 4, (8, 8)), (ph // 8 + 1, pw // 8 + 1))[:ph, :pw]
+    f = np.zeros((2, ph * 16, pw * 16), np.uint16)
+    f[0, ::16, ::16] = rng.integers(0, 4, (ph, pw))
+    f[1] = 65535
+    f[1, ::16, ::16] = 65532 + r
+    return np.ascontiguousarray(f[:, :h, :w])
+
+
+@pytest.mark.parametrize("levels,radius", [(4, 4), (5, 2)])   # level 3 the coarsest, and below another
+def test_costs_beyond_float64(levels, radius):
+    """Level-3 costs above 2^53 that float64 cannot tell apart: the sums over
+    the pieces have to be 64-bit integers."""
+    h, w, seed = 520, 536, 1
+    f = coherent_frames(h, w, seed)
+    d = synth.Desc(2, h, w, tile_size=16, black_level=0.0, white_level=65535.0, noise_a=1e-4, noise_b=1e-6)
+    params = {"levels": levels, "gate": 0.0, "lk_iterations": 0}
+    base, img = (oa.pyramid(oa.quad_sums(x), levels, 8) for x in f)
+    guess = np.zeros(oa.block_grid(base[3].shape, 8) + (2,), dtype=np.int64)
+    if levels == 5:
+        coarse = np.zeros(oa.block_grid(base[4].shape, 8) + (2,), dtype=np.int64)
+        guess = oa.upsample_guess(oa.match_level(base[4], img[4], 8, coarse, 4), 8, base[3].shape, 8)
+    vec = oa.match_level(base[3], img[3], 8, guess, radius)
+    largest, other = 0, 0
+    for by, bx in np.ndindex(vec.shape[:2]):
+        ys, xs = np.arange(8 * by, min(8 * by + 8, base[3].shape[0])), np.arange(8 * bx, min(8 * bx + 8, base[3].shape[1]))
+        keys = []
+        for dy in range(-radius, radius + 1):
+            for dx in range(-radius, radius + 1):
+                u = guess[by, bx] + (dx, dy)
+                e = img[3][np.ix_(np.clip(ys + u[1], 0, img[3].shape[0] - 1), np.clip(xs + u[0], 0, img[3].shape[1] - 1))]
+                e = e - base[3][np.ix_(ys, xs)]
+                largest = max(largest, int((e * e).sum()))
+                keys.append((sum(float((q * q).sum()) for q in e), dx * dx + dy * dy, len(keys), *u))   # float64 over the rows
+        other += tuple(vec[by, bx]) != min(keys)[3:]
+    assert largest > 2 ** 53 and other > 0   # float64 would decide some block otherwise
+    check_full(f, d, params, what=f"coherent {levels} levels")
