@@ -1077,12 +1077,12 @@ hipError_t match_rows(const int32_t* pyr, int2* vecs, const MatchLevel& ml, cons
 }
 
 // Block matching of one level by rows where that form exists (see
-// k_align_match_rows); false: the general kernel takes the level.
+// k_align_match_rows); false: the general kernel takes the level. (A level has
+// at most 2^28 pixels, so byte offsets are int, and blocks of 8 above level 0.)
 bool launch_match_rows(const int32_t* pyr, int2* vecs, const MatchLevel& ml, const AlignGeom& ag, int cus,
                        hipStream_t stream, hipError_t* err) {
-  if ((long long)ml.h * ml.w >= (1ll << 29)) return false;  // byte offsets are int
+  if (ml.level > 3) return false;
   const bool wide = ml.level == 3;
-  if (ml.level > 3 || (wide && ml.B != 8)) return false;
   if (ml.R == 2 && ml.B == 8 && !wide) *err = match_rows<8, 2, false>(pyr, vecs, ml, ag, cus, stream);
   else if (ml.R == 2 && ml.B == 8) *err = match_rows<8, 2, true>(pyr, vecs, ml, ag, cus, stream);
   else if (ml.R == 2 && ml.B == 16) *err = match_rows<16, 2, false>(pyr, vecs, ml, ag, cus, stream);

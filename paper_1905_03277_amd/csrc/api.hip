@@ -137,13 +137,11 @@ RobustConsts make_robust(const hmfsr_desc* d, const hmfsr_tuning* t) {
   return r;
 }
 
-MergeConsts make_merge(const hmfsr_desc* d, const hmfsr_tuning* t, const Geometry& g) {
+MergeConsts make_merge(const hmfsr_desc* d, const hmfsr_tuning* t) {
   MergeConsts m;
   m.om = make_omega(d, t);
   m.black = d->black_level;
   m.inv_range = (float)(1.0 / range_of(d));
-  m.col4 = 0;
-  for (int k = 0; k < 4; ++k) m.col4 |= g.colour[k] << (2 * k);
   return m;
 }
 
@@ -281,7 +279,7 @@ hmfsr_status run_merge(const hmfsr_desc* desc, const hmfsr_tuning* tuning, const
                        const Work& w, int shape, hipStream_t s, bool profiled) {
   const PriorConsts pc = make_prior(tuning);
   const RobustConsts rc = make_robust(desc, tuning);
-  const MergeConsts mc = make_merge(desc, tuning, g);
+  const MergeConsts mc = make_merge(desc, tuning);
   auto run = [&](int stage, auto fn) { return profiled ? timed(stage, s, fn) : fn(); };
   if (run_robust(g, rc, pc, frames, motion, w, w.rmin, nullptr, s, profiled) != hipSuccess) return HMFSR_E_HIP;
   if (run(HMFSR_STAGE_MERGE, [&] { return launch_merge(shape, g, mc, frames, motion, w.rmin, out, saved, s); }) !=
@@ -328,7 +326,7 @@ hmfsr_status hmfsr_stream_begin(const hmfsr_desc* desc, const hmfsr_tuning* tuni
   hipStream_t s = (hipStream_t)stream;
   // the base frame alone: its weights are 1 and it reads no motion or R_hat
   return timed(HMFSR_STAGE_MERGE, s, [&] {
-           return launch_merge_stream(g, make_merge(desc, tuning, g), base_frame, nullptr, nullptr, nullptr,
+           return launch_merge_stream(g, make_merge(desc, tuning), base_frame, nullptr, nullptr, nullptr,
                                       state, 0, s);
          }) == hipSuccess
              ? HMFSR_OK
@@ -363,7 +361,7 @@ hmfsr_status hmfsr_stream_add(const hmfsr_desc* desc, const hmfsr_tuning* tuning
   const Work w = work_carve(ws, g);
   const PriorConsts pc = make_prior(tuning);
   const RobustConsts rc = make_robust(desc, tuning);
-  const MergeConsts mc = make_merge(desc, tuning, g);
+  const MergeConsts mc = make_merge(desc, tuning);
   if (run_robust(g, rc, pc, frames, mo, w, w.rmin, nullptr, s, true) != hipSuccess ||
       timed(HMFSR_STAGE_MERGE, s, [&] {
         return launch_merge_stream(g, mc, frames, mo, w.rmin, state, state, 1, s);
@@ -381,7 +379,7 @@ hmfsr_status hmfsr_stream_end(const hmfsr_desc* desc, const hmfsr_tuning* tuning
   int dev = 0;
   if ((st = current_device(&dev)) != HMFSR_OK) return st;
   const Geometry g = make_geometry(desc);
-  return launch_stream_finish(g, make_merge(desc, tuning, g), state, out, (hipStream_t)stream) == hipSuccess
+  return launch_stream_finish(g, make_merge(desc, tuning), state, out, (hipStream_t)stream) == hipSuccess
              ? HMFSR_OK
              : HMFSR_E_HIP;
 }
@@ -409,7 +407,7 @@ hmfsr_status hmfsr_merge_backward(const hmfsr_desc* desc, const hmfsr_tuning* tu
   const BwdWork w = bwd_carve(ws, g, need_saved);
   const PriorConsts pc = make_prior(tuning);
   const RobustConsts rc = make_robust(desc, tuning);
-  const MergeConsts mc = make_merge(desc, tuning, g);
+  const MergeConsts mc = make_merge(desc, tuning);
   BwdConsts bc;
   bc.kd = tuning->k_detail;
   bc.kn = tuning->k_denoise;

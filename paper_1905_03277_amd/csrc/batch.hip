@@ -205,7 +205,7 @@ hmfsr_status hmfsr_autotune(const hmfsr_desc* desc, const hmfsr_tuning* tuning,
   // that merges of this size then run): one warm-up and three timed launches
   const int tiles = tiles_64x16(g.OH, g.OW);
   if ((st = run_merge(desc, tuning, g, frames, motion, out, nullptr, w, default_shape(tiles), s)) != HMFSR_OK) return st;
-  const MergeConsts mc = make_merge(desc, tuning, g);
+  const MergeConsts mc = make_merge(desc, tuning);
   hipEvent_t a = nullptr, b = nullptr;
   if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&b) != hipSuccess) return HMFSR_E_HIP;
   int best = kDefaultVariant;
@@ -331,7 +331,7 @@ hmfsr_status hmfsr_merge_batch(int32_t n_bursts, const hmfsr_desc* descs, const 
     a.gmu = w.gmu;
     a.gref = w.gref;
     a.g = geo[i];
-    a.mc = make_merge(&descs[i], &tunings[i], geo[i]);
+    a.mc = make_merge(&descs[i], &tunings[i]);
     a.rc = make_robust(&descs[i], &tunings[i]);
     a.pc = make_prior(&tunings[i]);
     a.merge_tiles_x = mtx[i];

@@ -46,7 +46,6 @@ struct RobustConsts {
 struct MergeConsts {
   OmegaConsts om;
   float black, inv_range;
-  int col4;  // colour of parity k in bits 2k..2k+1
 };
 
 // One burst of a batch, as the persistent kernels see it.

@@ -77,7 +77,7 @@ hmfsr_status validate(const hmfsr_desc* d, const hmfsr_tuning* t);
 Geometry make_geometry(const hmfsr_desc* d);
 PriorConsts make_prior(const hmfsr_tuning* t);
 RobustConsts make_robust(const hmfsr_desc* d, const hmfsr_tuning* t);
-MergeConsts make_merge(const hmfsr_desc* d, const hmfsr_tuning* t, const Geometry& g);
+MergeConsts make_merge(const hmfsr_desc* d, const hmfsr_tuning* t);
 OmegaConsts make_omega(const hmfsr_desc* d, const hmfsr_tuning* t);
 hmfsr_status current_device(int* dev_out);  // caller holds g_mutex
 hmfsr_status workspace(int dev, size_t bytes, hipStream_t stream, void** out);  // caller holds g_mutex

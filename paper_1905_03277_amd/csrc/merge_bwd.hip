@@ -461,14 +461,14 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
       if (slot) __syncthreads();  // the previous frame's windows are no longer read, its row sums complete
       if (!is_ref) {
         const int t = here(tid);
-  #pragma unroll
+#pragma unroll
         for (int i = 0; i < BRHT; ++i)
           if (t + i * BTHREADS < rhw * rhh) sm.sRh[t + i * BTHREADS] = rhv[i];
       }
       if (fi >= 2) add_rows(frame_of(fi - 1));  // frame 0 is the base frame: no sums
       // this frame's dL/drho and dL/dp of the thread's pixels (0 where skipped)
       float pgr[BPX], pgx[BPX], pgy[BPX];
-  #pragma unroll
+#pragma unroll
       for (int p = 0; p < BPX; ++p) pgr[p] = pgx[p] = pgy[p] = 0.f;
 
       const Win whole_w = make_win(bounds_of(slot), g);
@@ -508,9 +508,9 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
             const int I = min(max(or0 + r, 0), g.h - 1), J = min(max(oc0 + c, 0), g.w - 1);
             const int base = mul24(I - 1 - lr0, lw) + (J - 1 - lc0);  // the window's ring repeats the edges
             float l[3][3];
-  #pragma unroll
+#pragma unroll
             for (int a = 0; a < 3; ++a)
-  #pragma unroll
+#pragma unroll
               for (int bb = 0; bb < 3; ++bb) l[a][bb] = sm.sLum[base + a * lw + bb];
             double oxx, oxy, oyy;
             OmegaParts pt;
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
         __syncthreads();
 
         if (col_ok) {
-  #pragma unroll
+#pragma unroll
           for (int p = 0; p < BPX; ++p) {
             const int r = wave * BPX + p;
             if (r >= nrow) break;
@@ -559,7 +559,7 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
             const double fx = hx - fhj, fy = hy - fhi;
             const int ob = mul24((int)fhi - or0, ow) + ((int)fhj - oc0);
             double O[3], dOx[3], dOy[3];  // Omega_bar and its derivatives along hx, hy
-  #pragma unroll
+#pragma unroll
             for (int e = 0; e < 3; ++e) {
               const double o00 = sm.sOm[e][ob], o01 = sm.sOm[e][ob + 1];
               const double o10 = sm.sOm[e][ob + ow], o11 = sm.sOm[e][ob + ow + 1];
@@ -574,7 +574,7 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
             const double qa = O[2] * sc, qb2 = -2.0 * O[1] * sc, qc = O[0] * sc;
             double dx[3], dy[3];
             float dxf[3], dyf[3];  // offsets of in-frame samples, 0 elsewhere
-  #pragma unroll
+#pragma unroll
             for (int j = 0; j < 3; ++j) {
               dx[j] = ((double)j - 0.5) - frx;
               dy[j] = ((double)j - 0.5) - fry;
@@ -587,7 +587,7 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
             }
             // exponent of sample (i, j): (qa dx[j] + by[i]) dx[j] + cy[i], as the forward
             double cy[3], by[3];
-  #pragma unroll
+#pragma unroll
             for (int i = 0; i < 3; ++i) {
               by[i] = qb2 * dy[i];
               cy[i] = qc * (dy[i] * dy[i]);
@@ -607,9 +607,9 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
             const int vb = mul24(ic - 1 - rr0, rw) + (jc - 1 - rc0);
             float a[3][3];
             float grho = 0.f;
-  #pragma unroll
+#pragma unroll
             for (int i = 0; i < 3; ++i)
-  #pragma unroll
+#pragma unroll
               for (int j = 0; j < 3; ++j) {
                 const int q = (i == 1 && j == 1) ? 0 : (i == 1 ? 1 : (j == 1 ? 2 : 3));
                 const float w = __builtin_amdgcn_exp2f(
@@ -620,15 +620,15 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
               }
             // S = sum a d d^T, t = sum a d (offsets separate into columns and rows)
             float Acol[3], Arow[3], Sxy = 0.f;
-  #pragma unroll
+#pragma unroll
             for (int j = 0; j < 3; ++j) Acol[j] = a[0][j] + a[1][j] + a[2][j];
-  #pragma unroll
+#pragma unroll
             for (int i = 0; i < 3; ++i) {
               Arow[i] = a[i][0] + a[i][1] + a[i][2];
               Sxy = fmaf(dyf[i], fmaf(a[i][0], dxf[0], fmaf(a[i][1], dxf[1], a[i][2] * dxf[2])), Sxy);
             }
             float Sxx = 0.f, Syy = 0.f, tx = 0.f, ty = 0.f;
-  #pragma unroll
+#pragma unroll
             for (int j = 0; j < 3; ++j) {
               tx = fmaf(Acol[j], dxf[j], tx);
               Sxx = fmaf(Acol[j] * dxf[j], dxf[j], Sxx);
@@ -656,7 +656,7 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
             const float wq[4] = {(1.f - ffx) * (1.f - ffy), ffx * (1.f - ffy), (1.f - ffx) * ffy, ffx * ffy};
             const int cq[4] = {ob, ob + 1, ob + ow, ob + ow + 1};
             float s6[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  #pragma unroll
+#pragma unroll
             for (int q = 0; q < 4; ++q) {
               const double2 dir = sm.sDir[cq[q]];
               const float4 P0 = sm.sP[0][cq[q]], P1 = sm.sP[1][cq[q]];
@@ -670,7 +670,7 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
               s6[4] = fmaf(k1, P1.x, s6[4]);
               s6[5] = fmaf(k2, P1.y, s6[5]);
             }
-  #pragma unroll
+#pragma unroll
             for (int e = 0; e < 6; ++e) acc[e] += (double)s6[e];
             pgr[p] = grho;
             pgx[p] = gpx;
@@ -691,7 +691,7 @@ __global__ __launch_bounds__(BTHREADS, 3) void k_merge_bwd(
         const bool end_t = (runs >> 7) & 1, end_a = (runs >> 15) & 1, end_b = (runs >> 23) & 1;
         bool joined = false;
         if (BPX == 2) joined = r0 + 1 >= nrow || sm.sTyRow[r0] == sm.sTyRow[r0 + 1];  // uniform
-  #pragma unroll
+#pragma unroll
         for (int p = 0; p < BPX; ++p) {
           const int r = r0 + p;
           if (r >= nrow) continue;  // uniform
@@ -1003,10 +1003,10 @@ __global__ __launch_bounds__(64, 5) void k_robust_bwd(const uint2* __restrict__ 
           }
         const float Rv = sR[i - bi0 + 4][j - bj0 + 4];
         if (gR != 0.f && Rv > 0.f && Rv < 1.f) {  // unclamped R of eq. (5)
-      const float gi = gref[(size_t)ic * g.w + jc];
-      const uint2 er = mref[(size_t)ic * ws + jc + 1];
-      const uint2 eA = mfr[(size_t)ya * ws + xa + 1], eB = mfr[(size_t)ya * ws + xb + 1];
-      const uint2 eC = mfr[(size_t)yb * ws + xa + 1], eD = mfr[(size_t)yb * ws + xb + 1];
+          const float gi = gref[(size_t)ic * g.w + jc];
+          const uint2 er = mref[(size_t)ic * ws + jc + 1];
+          const uint2 eA = mfr[(size_t)ya * ws + xa + 1], eB = mfr[(size_t)ya * ws + xb + 1];
+          const uint2 eC = mfr[(size_t)yb * ws + xa + 1], eD = mfr[(size_t)yb * ws + xb + 1];
           const float inv = fabsf(gi);  // 1 / sum_c sigma_c^2, eq. (5)
           float mu_ref[3], dmd2[3];
           guide_means(er, mu_ref);

@@ -53,8 +53,6 @@ struct Caps {
   static constexpr int VT = TX * TY;
 };
 
-__device__ __forceinline__ int colour_of(int col4, int parity) { return (col4 >> (2 * parity)) & 3; }
-
 // R_hat is interpolated between the values a and b of neighbouring cells at
 // fraction f of a cell. It is 0 where a frame is rejected: beside such a cell
 // (b = 0) the weight 1 - f is the frame's whole weight, whose relative value

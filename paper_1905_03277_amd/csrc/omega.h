@@ -25,7 +25,7 @@ struct OmegaConsts {
 };
 
 // The hardware reciprocal and reciprocal square root are good to ~5e-8
-// relative; one Newton step takes them to ~4e-15, two to the last bit or two.
+// relative; one Newton step takes them to ~4e-15.
 
 // 1 / d to ~2e-15 relative (one Newton step), for values that feed only
 // continuous arithmetic.
@@ -39,22 +39,6 @@ __device__ __forceinline__ double rsqrt64_1(double x) {
   const double y = __builtin_amdgcn_rsq(x);
   return y * fma(-0.5 * x, y * y, 1.5);
 }
-
-// 1 / sqrt(x) for x > 0 to ~2 ulp: the hardware reciprocal square root
-// refined by two Newton steps.
-__device__ __forceinline__ double rsqrt64(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  y = y * fma(-0.5 * x, y * y, 1.5);
-  return y * fma(-0.5 * x, y * y, 1.5);
-}
-
-// sqrt(x) for x >= 0 to ~1e-15 relative (the correctly rounded library
-// square root costs twice as many instructions, and nothing here needs the
-// last bit).
-__device__ __forceinline__ double sqrt64(double x) { return x > 0.0 ? x * rsqrt64(x) : 0.0; }
-
-// sqrt(x) for x >= 0 to ~4e-15 relative (one Newton step).
-__device__ __forceinline__ double sqrt64_1(double x) { return x > 0.0 ? x * rsqrt64_1(x) : 0.0; }
 
 // What the adjoint needs of one pixel's kernel covariance besides Omega.
 struct OmegaParts {
@@ -91,8 +75,8 @@ __device__ __forceinline__ void omega_core(const Q (&l)[3][3], const OmegaConsts
   const double half = 0.5 * (txx - tyy);
   const double r2 = half * half + txy * txy;
   const double tr = txx + tyy;
-  // (tr and r2 are 0 or at least 1, being sums of integer products and their
-  // halves: the bounds below change nothing but what 0 would divide)
+  // (tr is 0 or at least 1 and r2 0 or at least 1/4, from sums of integer
+  // products: the bounds below change nothing but what 0 would divide)
   const bool some = r2 > 0.0;
   const double y = rsqrt64_1(fmax(r2, 1e-300));  // 1 / rad
   const double rad = r2 * y;
