@@ -662,6 +662,8 @@ def main():
                      "kernel": dom, "kernel_ms": round(kern_ms[dom], 4),
                      "algorithmic_ops": ops[dom]},
         "kernels_ms": {k: round(v, 4) for k, v in kern_ms.items()},
+        "kernels_ms_launches": "k_prior and k_robust (guide statistics and robustness) timed as launches of their own; "
+                               "a merge outside this timing runs prior and statistics in one launch",
         "hbm": {"algorithmic_bytes": byts["total"],
                 "achieved_GBs": round(byts["total"] / (ms / 1e3) / 1e9, 1),
                 "peak_GBs": HBM_PEAK_GBS,

@@ -443,18 +443,20 @@ hmfsr_status hmfsr_autotune(const hmfsr_desc* desc, const hmfsr_tuning* tuning,
 /*
  * Per-stage GPU timing (the tracing aid of the library). Between
  * hmfsr_profile_begin() and hmfsr_profile_end(), every kernel launch is
- * bracketed by a pair of HIP events recorded on the call's own stream;
+ * bracketed by a pair of HIP events recorded on the call's own stream (a
+ * merge's motion prior and guide statistics, one launch otherwise, are launches
+ * of their own meanwhile, the statistics timed with the robustness);
  * hmfsr_profile_end() waits for the recorded events, adds up the elapsed
  * times per stage and turns the recording off. Not meant for use while other
  * threads issue merges.
  */
 enum {
   HMFSR_STAGE_PRIOR = 0,  /* motion prior per tile (eq. 7-8)           */
-  HMFSR_STAGE_ROBUST = 1, /* robustness and its 5x5 minimum (eq. 5-9)  */
+  HMFSR_STAGE_ROBUST = 1, /* guide statistics, robustness and its 5x5 minimum (eq. 5-9) */
   HMFSR_STAGE_MERGE = 2,  /* kernel-regression accumulation (eq. 1-4)  */
   HMFSR_STAGE_BATCH = 3,  /* one replay of a batched-merge graph       */
   HMFSR_STAGE_MERGE_BWD = 4,   /* adjoint of the accumulation              */
-  HMFSR_STAGE_ROBUST_BWD = 5,  /* adjoint of the robustness                */
+  HMFSR_STAGE_ROBUST_BWD = 5,  /* adjoint of the robustness, sums of the motion gradient */
   HMFSR_STAGE_GRAD_REDUCE = 6, /* fixed-order sums of the tuning gradient */
   HMFSR_STAGE_ALIGN = 7,       /* tile alignment (pyramid, matching, Lucas-Kanade) */
   HMFSR_NUM_STAGES = 8

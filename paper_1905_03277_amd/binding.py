@@ -28,6 +28,8 @@ EXPORTED = ("hmfsr_merge", "hmfsr_merge_noalloc", "hmfsr_merge_backward", "hmfsr
 STAGE_PRIOR, STAGE_ROBUST, STAGE_MERGE, STAGE_BATCH = 0, 1, 2, 3
 STAGE_MERGE_BWD, STAGE_ROBUST_BWD, STAGE_GRAD_REDUCE, STAGE_ALIGN = 4, 5, 6, 7
 NUM_STAGES = 8
+# (stages, not kernels: k_grad_reduce is the tuning gradient's sums, k_robust_bwd
+# also adds up the motion gradient, k_robust includes the guide statistics)
 STAGE_NAMES = {STAGE_PRIOR: "k_prior", STAGE_ROBUST: "k_robust", STAGE_MERGE: "k_merge",
                STAGE_BATCH: "batch_graph", STAGE_MERGE_BWD: "k_merge_bwd",
                STAGE_ROBUST_BWD: "k_robust_bwd", STAGE_GRAD_REDUCE: "k_grad_reduce",

@@ -346,7 +346,7 @@ __global__ __launch_bounds__(256) void k_align_match(const int32_t* __restrict__
 // per SIMD (13 KB of LDS a wave), the loads' latency. With a candidate per
 // lane and the block and its search region in LDS (two reads, a conversion and
 // index arithmetic per candidate and pixel) 12 MP x 8 took 245 us on level 0,
-// now 105; 5 x 510 x 766 with 32-pixel tiles took 38 us on the coarsest level
+// now 107; 5 x 510 x 766 with 32-pixel tiles took 38 us on the coarsest level
 // and 26 on each other one, now 11 and 7.5.
 template <int B>
 struct RowBlocks {
@@ -840,7 +840,8 @@ __global__ __launch_bounds__(256) void k_align_lk(const int32_t* __restrict__ py
 // the loads' latency at three waves per SIMD (152 VGPRs). Windows copied to
 // LDS by flat index took 2100 VALU instructions per wave and pass of four
 // tiles, 381 us at 12 MP x 8 and 28 us at 5 x 510 x 766 (32-pixel tiles); this
-// takes 1090, 260 and 22 us. Three one-word loads instead of one 12-byte load
+// takes 1090, 208 and 21 us (260 at 12 MP x 8 while the base frame had passes
+// of its own). Three one-word loads instead of one 12-byte load
 // per row, or neighbour columns from the adjacent lanes: 3 and 8 % slower
 // alignment; four rows ahead: registers spill (0.48 -> 0.67 ms).
 template <int WIN>

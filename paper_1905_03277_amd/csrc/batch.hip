@@ -341,7 +341,9 @@ hmfsr_status hmfsr_merge_batch(int32_t n_bursts, const hmfsr_desc* descs, const 
   // same shapes as the captured graph: refresh arguments, replay. The graph's
   // launches depend on the descriptors alone (noise tables' addresses aside),
   // the buffers lie in the argument blocks (descriptors and tunings are plain
-  // int32 / float structs: memcmp is exact).
+  // int32 / float structs: memcmp is exact). A graph built with the LDS of S.3
+  // is kept when no burst asks for it any more: a batch of twelve then takes
+  // 1516 instead of 1510 us, a rebuild 150 us and a wait.
   std::vector<const void*> ptrs;
   std::vector<hmfsr_desc> shapes(descs, descs + n_bursts);
   bool any_hf = false;

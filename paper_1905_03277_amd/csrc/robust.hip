@@ -326,9 +326,12 @@ __global__ __launch_bounds__(THREADS) void k_base_stats(const uint16_t* __restri
 // The three do not depend on each other, and for small bursts each was a
 // launch of 4.5-5 us for 1-3 us of work. Without S.3 the base tiles take 16 KB
 // of LDS (the 32 KB they took before also without it would hold the streaming
-// part to four workgroups per unit), so one launch is the faster form at every
+// part to five workgroups per unit), so one launch is the faster form at every
 // size: the 8 x 256 x 256 merge 68.9 -> 59.9 us, 5 x 750 x 1002 at scale 1.5
-// 118 -> 110 us, 12 MP x 8 989 -> 976 us, 3 MP x 8 streamed 673 -> 612 us.
+// 118 -> 110 us, 12 MP x 8 989 -> 976 us, 3 MP x 8 streamed 673 -> 612 us. With
+// S.3, whose 32 KB every workgroup is given, it is too: 8 x 256 x 256 54.5 ->
+// 43.1 us, 3 MP x 8 294 -> 286, 12 MP x 8 1017 -> 1008, 3 MP x 8 streamed 664
+// -> 615, the adjoint of 8 x 768 x 1024 266 -> 255.
 __global__ __launch_bounds__(THREADS) void k_guide(const uint16_t* __restrict__ frames,
                                                    const float* __restrict__ motion, Geometry g, RobustConsts rc,
                                                    PriorConsts pc, uint2* __restrict__ gmu, float* __restrict__ gref,
